@@ -1,6 +1,7 @@
 // Host side of the respec_verify C ABI: plan creation (tiling choices and
 // workspace layout), argument validation and the launch sequence of one
 // verification step.  See include/respec_verify.h for the contract.
+#include <limits.h>
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
@@ -18,18 +19,12 @@ struct respec_verify_plan {
   respec_verify_shape s;
   int es;                 // bytes per element of the workload dtype
   int group;              // Hq / Hkv
-  // attention tiling
-  int nb, wr, wk, rows_per_wg, n_rowblk, attn_threads, nsplit_cap;
-  int attn_shared;        // bf16 with several waves of rows per KV head: KV tiles shared through LDS
-  int attn_stages;        // ring slots of the shared-tile kernel
-  int attn_kg;            // key groups of the shared-tile kernel
-  int attn_wg_target;     // workgroups the splits aim for
-  int flat_pieces;        // ragged batches (register path): pieces of each head's KV tiles
-  size_t attn_lds;
   // vocabulary statistics: tiles of the LM head and the top-K width (8 or 16)
   int ko, n_vtiles;
   // workspace layout (bytes)
   size_t off_po, off_pm, off_pl, off_x, off_part, off_flag, off_cnt, off_stoch, off_rank;
+  size_t off_span;        // first and last piece of each sequence (dead before the LM head's statistics)
+  size_t part_total;      // rows of attention partials that the workspace holds
   size_t n_cnt_seq, total;
   // the attention kernel's LDS limit is raised on the first step (plan creation stays GPU-free)
   mutable std::atomic<bool> lds_ready{false};
@@ -43,6 +38,33 @@ constexpr int kCUs = 256;
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
+// Register-path attention (tree_attn_kernel) of `rows` query rows per KV head:
+// rows are (node, head-in-group) pairs; a wave owns at most 32 of them (more
+// would not fit the registers next to a ring of tiles); above 4 waves' worth a
+// head's KV rows are read once per row block.
+struct RowGeom {
+  int nb, wr, wk, rows_per_wg, n_rowblk, threads;
+  size_t lds;
+};
+RowGeom row_geom(int es, int head_dim, int rows) {
+  RowGeom g;
+  g.nb = rows <= 16 ? 1 : 2;
+  const int rb = 16 * g.nb, rg = cdiv(rows, rb);
+  g.wr = rg < 4 ? rg : 4;
+  g.n_rowblk = cdiv(rg, g.wr);
+  g.wk = clampi(min(4 / g.wr, 128 / (g.wr * rb)), 1, 4);
+  g.rows_per_wg = g.wr * rb;
+  const int nwaves = g.wr * g.wk;
+  g.threads = 64 * nwaves;
+  // per wave: one row-major, swizzled V tile (bf16) or one transposed, padded V tile (float32)
+  const size_t vt = es == 2 ? (size_t)nwaves * kKvTile * head_dim * es
+                            : (size_t)nwaves * head_dim * (kKvTile + kVtPad) * es;
+  // wave merge: every wave's O lane-major (D/16 x NB blocks of 64 x 16 bytes) plus its m and l
+  const size_t merge =
+      g.wk > 1 ? (size_t)nwaves * ((size_t)(head_dim / 16) * g.nb * 64 * 16 + (size_t)2 * g.nb * 64 * 4) : 0;
+  g.lds = max(vt, merge);
+  return g;
+}
 bool aligned(const void* p, size_t n) { return ((uintptr_t)p % n) == 0; }
 
 }  // namespace
@@ -101,66 +123,39 @@ respec_status respec_verify_create(const respec_verify_shape* shape, respec_veri
   p->es = es;
   p->group = s.n_q_heads / s.n_kv_heads;
 
-  // attention: rows of a KV head are (node, head-in-group) pairs; a wave owns
-  // at most 32 of them (more would not fit the registers next to a ring of
-  // tiles); above 4 waves' worth a head's KV rows are read once per row block
+  // attention partials: rows of every split (or piece) of the largest tree
   const int rmax = s.max_nodes * p->group;
-  const int nb = rmax <= 16 ? 1 : 2;
-  const int rg = cdiv(rmax, 16 * nb);
-  const int rb = 16 * nb;
   const long long t_cap = (long long)s.max_kv_len + s.max_nodes;
-  p->nb = nb;
-  p->attn_shared = es == 2 && rg >= 2;
-  if (p->attn_shared) {
-    // up to 8 waves of rows read every KV tile once, from a shared LDS ring,
-    // one workgroup per CU; up to 4 waves of rows, a second key group of as
-    // many waves takes every other tile (one workgroup fills the CU, and its
-    // two halves stay in step)
-    p->wr = rg < 8 ? rg : 8;
-    p->n_rowblk = cdiv(rg, p->wr);
-    p->wk = 1;
-    p->attn_kg = p->wr <= 4 ? 2 : 1;
-    p->rows_per_wg = p->wr * rb;
-    p->attn_threads = 64 * p->wr * p->attn_kg;
-    p->attn_stages = p->attn_kg == 1 ? kSharedStages1 : kSharedStages2;
-    p->attn_lds = (size_t)shared_ring_bytes(s.head_dim, p->attn_stages);
-    p->attn_wg_target = kCUs;
+  int rows_per_wg, n_rowblk, slots;
+  if (es == 2 && rmax > 32) {
+    const int rg = cdiv(rmax, 32), wr = rg < 8 ? rg : 8;
+    n_rowblk = cdiv(rg, wr);
+    rows_per_wg = 32 * wr;
+    slots = clampi(kCUs / (s.n_kv_heads * n_rowblk), 1, cdiv(t_cap, kKvTile));
   } else {
-    p->wr = rg < 4 ? rg : 4;
-    p->n_rowblk = cdiv(rg, p->wr);
-    int wk = 4 / p->wr;
-    if (wk > 128 / (p->wr * rb)) wk = 128 / (p->wr * rb);
-    p->wk = wk < 1 ? 1 : wk;
-    p->rows_per_wg = p->wr * rb;
-    const int nwaves = p->wr * p->wk;
-    p->attn_threads = 64 * nwaves;
-    // per wave: one row-major, swizzled V tile (bf16) or one transposed, padded V tile (float32)
-    const size_t vt_bytes = es == 2 ? (size_t)nwaves * kKvTile * s.head_dim * es
-                                    : (size_t)nwaves * s.head_dim * (kKvTile + kVtPad) * es;
-    // wave merge: every wave's O lane-major (D/16 x NB blocks of 64 x 16 bytes) plus its m and l
-    const size_t merge_bytes =
-        p->wk > 1 ? (size_t)nwaves * ((size_t)(s.head_dim / 16) * p->nb * 64 * 16 + (size_t)2 * p->nb * 64 * 4) : 0;
-    p->attn_lds = vt_bytes > merge_bytes ? vt_bytes : merge_bytes;
-    p->attn_wg_target = kTargetWaves / nwaves;
+    const RowGeom ge = row_geom(es, s.head_dim, rmax);
+    n_rowblk = ge.n_rowblk;
+    rows_per_wg = ge.rows_per_wg;
+    const int target = kTargetWaves / (ge.threads / 64) / (s.n_kv_heads * n_rowblk);
+    slots = max(clampi(target, 1, cdiv(t_cap, kKvTile)), clampi(target, 1, 64));
   }
-  const int per_split = s.n_kv_heads * p->n_rowblk;
-  p->nsplit_cap = clampi(p->attn_wg_target / per_split, 1, cdiv(t_cap, kKvTile));
-  // one piece per CU (two per CU measured slower on an 8-sequence ragged batch: 158 against 144 us)
-  p->flat_pieces = p->attn_shared ? 0 : clampi(p->attn_wg_target / per_split, 1, 64);
-  const int slots = p->nsplit_cap > p->flat_pieces ? p->nsplit_cap : p->flat_pieces;
 
   p->ko = s.topk_out <= 8 ? 8 : 16;
   p->n_vtiles = cdiv(s.vocab, kLmTileRows);
 
   // workspace
   const size_t mcap = (size_t)s.max_batch * s.max_nodes;
-  const size_t prow = (size_t)s.max_batch * s.n_kv_heads * p->n_rowblk * slots * p->rows_per_wg;
+  const size_t prow = (size_t)s.max_batch * s.n_kv_heads * n_rowblk * slots * rows_per_wg;
   size_t off = 0;
   p->off_po = off; off = align256(off + prow * s.head_dim * 4);
   p->off_pm = off; off = align256(off + prow * 4);
   p->off_pl = off; off = align256(off + prow * 4);
   p->off_x = off; off = align256(off + mcap * s.hidden * es);
-  p->off_part = off; off = align256(off + mcap * p->n_vtiles * kTileWords * 4);
+  p->part_total = prow;
+  const size_t part_bytes = mcap * p->n_vtiles * kTileWords * 4;
+  const size_t span_bytes = (size_t)s.max_batch * s.n_kv_heads * cdiv(rmax, 256) * 8;
+  p->off_span = off;  // shared with the LM head's statistics, which are written after the split merge
+  p->off_part = off; off = align256(off + (part_bytes > span_bytes ? part_bytes : span_bytes));
   p->off_flag = off; off = align256(off + mcap * 4);
   p->n_cnt_seq = s.max_batch;
   p->off_cnt = off; off = align256(off + p->n_cnt_seq * 4);
@@ -187,6 +182,25 @@ respec_status respec_verify_workspace_init(const respec_verify_plan* plan, void*
 }  // extern "C"
 
 namespace {
+
+// Streaming attention of a step whose largest tree has n nodes.
+struct StreamGeom {
+  int wr, kg, n_rowblk, part_rows, pieces, slices;
+};
+StreamGeom stream_geom(const respec_verify_plan* p, int n, int batch) {
+  StreamGeom g;
+  const int rows = n * p->group, rg = cdiv(rows, 32);
+  g.n_rowblk = cdiv(rg, 8);
+  g.wr = cdiv(rg, g.n_rowblk);
+  g.kg = g.wr <= 2 ? 4 : g.wr <= 4 ? 2 : 1;
+  g.part_rows = g.n_rowblk == 1 ? rows : g.wr * 32;
+  g.slices = cdiv(batch, kStreamSlice);
+  const int heads = p->s.n_kv_heads * g.n_rowblk;
+  // one workgroup per CU, within the partial rows that the workspace holds
+  const long long blocks = (long long)(p->part_total / ((size_t)heads * g.part_rows));
+  g.pieces = (int)max(1ll, min((long long)(kCUs / heads), (blocks - batch) / g.slices + 1));
+  return g;
+}
 
 // One step on workspace `ws` (the plan's layout) with the sequences' completion
 // counters at `cnt` (zero between steps).
@@ -239,9 +253,11 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
 
 
   if (!plan->lds_ready.load(std::memory_order_acquire)) {
-    const hipError_t e = plan->attn_shared ? set_tree_attn_shared_lds_limit(s.head_dim, plan->attn_stages, plan->attn_kg, plan->attn_lds)
-                                           : set_tree_attn_lds_limit(s.dtype, s.head_dim, plan->nb, plan->attn_lds);
-    if (e != hipSuccess) return RESPEC_ERR_HIP;
+    for (int rows : {16, 32}) {  // (both row block counts; more row waves need no more)
+      const RowGeom ge = row_geom(plan->es, s.head_dim, rows);
+      if (set_tree_attn_lds_limit(s.dtype, s.head_dim, ge.nb, ge.lds) != hipSuccess) return RESPEC_ERR_HIP;
+    }
+    if (plan->es == 2 && set_tree_attn_stream_lds_limit(s.head_dim) != hipSuccess) return RESPEC_ERR_HIP;
     plan->lds_ready.store(true, std::memory_order_release);
   }
 
@@ -265,39 +281,59 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
   at.group = plan->group;
   at.kv_cap = a.kv_capacity;
   at.max_nodes = a.max_nodes_in_batch;
-  const long long t_max = (long long)a.max_kv_len_in_batch + a.max_nodes_in_batch;
-  const int per_split = a.batch * s.n_kv_heads * plan->n_rowblk;
-  const int target = clampi(plan->attn_wg_target / per_split, 1, plan->nsplit_cap);
-  // (a split holds at least one tile per key-group wave: fewer, fuller splits for short caches)
-  at.chunk = max(cdiv(cdiv(t_max, target), kKvTile), plan->attn_shared ? plan->attn_kg : plan->wk) * kKvTile;
-  at.nsplit = cdiv(t_max, at.chunk);
-  at.flat = 0;
   at.batch = a.batch;
-  // Ragged batches on the register path: each head's KV tiles over every sequence are cut
-  // into equal pieces, one workgroup each, so that the longest sequence does not finish
-  // alone (per-sequence splits leave every other workgroup idle at the end).
-  const bool flat = !plan->attn_shared && a.batch > 1 && a.batch <= 64;
-  if (flat) {
-    at.flat = plan->flat_pieces;
-    at.nsplit = at.flat;
-    at.chunk = 0;
-  }
-  at.n_rowblk = plan->n_rowblk;
-  at.rows_per_wg = plan->rows_per_wg;
-  at.wr = plan->wr;
-  at.wk = plan->wk;
+  at.pieces = 0;
+  at.flat = 0;
   at.scale_log2 = (float)(1.4426950408889634 / sqrt((double)s.head_dim));
-  dim3 agrid(at.nsplit, s.n_kv_heads * plan->n_rowblk, flat ? 1 : a.batch);
+  const int rows = a.max_nodes_in_batch * plan->group;  // query rows per KV head
   hipError_t ae;
-  if (plan->attn_shared)
-    ae = launch_tree_attn_shared(s.head_dim, plan->nb, plan->attn_stages, plan->attn_kg, agrid, plan->attn_threads,
-                                 plan->attn_lds, at, st, ev ? ev[0] : nullptr);
-  else
-    ae = launch_tree_attn(s.dtype, s.head_dim, plan->nb, agrid, plan->attn_threads, plan->attn_lds, at, st,
-                          ev ? ev[0] : nullptr);
+  int merge_rows_per_blk;
+  if (plan->es == 2 && rows > 32) {
+    // more than one wave of rows: KV tiles shared through LDS.  Up to 32 rows the
+    // register path's four independent waves per workgroup are as fast or faster:
+    // 26 nodes over 2048 rows of 32 heads 13.5 us against 15.7 us, 96 sequences of
+    // 1-12 nodes over 100-1500 rows 184 us against 196 us.
+    const StreamGeom ge = stream_geom(plan, a.max_nodes_in_batch, a.batch);
+    at.wr = ge.wr;
+    at.n_rowblk = ge.n_rowblk;
+    at.rows_per_wg = ge.wr * 32;
+    merge_rows_per_blk = at.part_rows = ge.part_rows;
+    at.pieces = ge.pieces;
+    at.part_blocks = ge.slices * (ge.pieces - 1) + a.batch;
+    at.span = reinterpret_cast<int32_t*>(ws + plan->off_span);
+    ae = launch_tree_attn_stream(s.head_dim, ge.kg, dim3(ge.pieces, s.n_kv_heads * ge.n_rowblk, ge.slices), at, st,
+                                 ev ? ev[0] : nullptr);
+  } else {
+    const RowGeom ge = row_geom(plan->es, s.head_dim, rows);
+    const int heads = s.n_kv_heads * ge.n_rowblk;
+    // splits (or pieces) whose partials the workspace holds
+    const int held = (int)min(plan->part_total / ((size_t)a.batch * heads * ge.rows_per_wg), (size_t)INT_MAX);
+    const int wg_target = kTargetWaves / (ge.threads / 64);
+    const long long t_max = (long long)a.max_kv_len_in_batch + a.max_nodes_in_batch;
+    const int target = clampi(wg_target / (a.batch * heads), 1, min(held, cdiv(t_max, kKvTile)));
+    // (a split holds at least one tile per key-group wave: fewer, fuller splits for short caches)
+    at.chunk = max(cdiv(cdiv(t_max, target), kKvTile), ge.wk) * kKvTile;
+    at.nsplit = cdiv(t_max, at.chunk);
+    // Ragged batches: each head's KV tiles over every sequence are cut into
+    // equal pieces, one workgroup each and one piece per CU, so that the longest
+    // sequence does not finish alone (per-sequence splits leave every other
+    // workgroup idle at the end; two pieces per CU measured slower on an
+    // 8-sequence ragged batch: 158 against 144 us).
+    const bool flat = a.batch > 1 && a.batch <= 64;
+    if (flat) {
+      at.flat = at.nsplit = clampi(wg_target / heads, 1, min(held, 64));
+      at.chunk = 0;
+    }
+    at.n_rowblk = ge.n_rowblk;
+    merge_rows_per_blk = at.rows_per_wg = ge.rows_per_wg;
+    at.wr = ge.wr;
+    at.wk = ge.wk;
+    ae = launch_tree_attn(s.dtype, s.head_dim, ge.nb, dim3(at.nsplit, heads, flat ? 1 : a.batch), ge.threads, ge.lds,
+                          at, st, ev ? ev[0] : nullptr);
+  }
   if (ae != hipSuccess) return RESPEC_ERR_HIP;
   const int merge_rows = 256 / (s.head_dim / 4);
-  dim3 mgrid(cdiv(plan->rows_per_wg, merge_rows), a.batch * s.n_kv_heads * plan->n_rowblk);
+  dim3 mgrid(cdiv(merge_rows_per_blk, merge_rows), a.batch * s.n_kv_heads * at.n_rowblk);
   if (launch_attn_merge(s.dtype, s.head_dim, mgrid, at, st, ev ? ev[1] : nullptr) != hipSuccess)
     return RESPEC_ERR_HIP;
 

@@ -34,7 +34,15 @@ struct AttnArgs {
   // 0: blockIdx.x is a split of `chunk` rows of sequence blockIdx.z
   int32_t flat;
   int32_t batch;
+  // streaming kernel (bf16): pieces per (KV head, row block) and slice of sequences; a segment's
+  // partial block is slice * (pieces - 1) + piece + sequence, of part_blocks per (head, row block),
+  // each part_rows rows; span [B][Hkv][n_rowblk][2]: first and last piece of each sequence.
+  // pieces == 0: the partials of tree_attn_kernel.
+  int32_t pieces, part_blocks, part_rows;
+  int32_t* span;
 };
+
+constexpr int kStreamSlice = 256;  // sequences per slice of the streaming kernel
 
 struct LmArgs {
   const void* x;           // [M][Hd]
@@ -120,15 +128,11 @@ hipError_t launch_tree_attn(int dtype, int head_dim, int nb, dim3 grid, int thre
 hipError_t set_tree_attn_lds_limit(int dtype, int head_dim, int nb, size_t lds);
 hipError_t launch_attn_merge(int dtype, int head_dim, dim3 grid, const AttnArgs& a, hipStream_t s,
                              hipEvent_t ev_stop = nullptr);
-// bf16 only; a.wr waves of 32 query rows each (nb = 2) in each of kg (1 or 2)
-// key groups, 2-8 waves in all; KV tiles shared through an LDS ring of
-// `stages` (8) K+V tiles
-hipError_t launch_tree_attn_shared(int head_dim, int nb, int stages, int kg, dim3 grid, int threads, size_t lds,
-                                   const AttnArgs& a, hipStream_t s, hipEvent_t ev_start = nullptr);
-hipError_t set_tree_attn_shared_lds_limit(int head_dim, int stages, int kg, size_t lds);
-constexpr int shared_ring_bytes(int head_dim, int stages) { return stages * 2 * kKvTile * head_dim * 2; }
-constexpr int kSharedStages1 = 10;  // ring slots of the shared-tile kernel with one key group (160 KB at head_dim 128)
-constexpr int kSharedStages2 = 10;  // ... and with two key groups
+// bf16 streaming kernel: a.wr row waves (1..8) of 32 query rows in each of kg key groups
+// (4 for wr <= 2, 2 for wr <= 4, 1), grid (pieces, Hkv * n_rowblk, slices of kStreamSlice sequences)
+hipError_t launch_tree_attn_stream(int head_dim, int kg, dim3 grid, const AttnArgs& a, hipStream_t s,
+                                   hipEvent_t ev_start = nullptr);
+hipError_t set_tree_attn_stream_lds_limit(int head_dim);
 // mb: 16-row token blocks per workgroup (1-4 plain, 8 and 16 GEMM); wide: bf16 with up to 64 token
 // rows in the GEMM kernel's 256-row vocabulary tiles (n_mtiles = 1)
 hipError_t launch_lmhead(int dtype, int mb, bool wide, const LmArgs& a, hipStream_t s, hipEvent_t ev_stop = nullptr);
