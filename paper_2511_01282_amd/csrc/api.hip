@@ -33,7 +33,6 @@ struct respec_verify_plan {
 namespace {
 
 constexpr int kTargetWaves = 1024;  // attention: one wave per SIMD on a 256-CU MI355X
-constexpr int kCUs = 256;
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
@@ -346,18 +345,11 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
     lm.m_rows = a.total_nodes;
     lm.vocab = s.vocab;
     lm.hidden_size = s.hidden;
-    // token rows per workgroup 16*mb: up to 64 in the plain kernel, 128 or 256
-    // in the GEMM one (bf16), so that W is streamed once for up to 256 rows.  A vocabulary of more 64-row tiles than two per CU takes
-    // the GEMM kernel's 256-row vocabulary tiles (bf16): each x row then serves
-    // four times as many W rows.
-    const int M = a.total_nodes;
-    int mb = M <= 16 ? 1 : M <= 32 ? 2 : M <= 48 ? 3 : 4;
-    if (M > 64 && s.dtype == RESPEC_BF16) mb = M <= 128 ? 8 : 16;
-    const bool wide = s.dtype == RESPEC_BF16 && M <= 64 && plan->n_vtiles > 2 * kCUs;
-    lm.n_mtiles = wide ? 1 : cdiv(M, 16 * mb);
+    const LmTile tile = lm_tile(s.dtype, a.total_nodes, s.vocab);
+    lm.n_mtiles = cdiv(a.total_nodes, lm_tile_rows(tile));
     lm.partials = vocab_pass ? reinterpret_cast<float*>(ws + plan->off_part) : nullptr;
     lm.n_vtiles = plan->n_vtiles;
-    if (launch_lmhead(s.dtype, mb, wide, lm, st, ev ? ev[2] : nullptr) != hipSuccess) return RESPEC_ERR_HIP;
+    if (launch_lmhead(s.dtype, tile, lm, st, ev ? ev[2] : nullptr) != hipSuccess) return RESPEC_ERR_HIP;
   } else if (ev && hipEventRecord(ev[2], st) != hipSuccess) {
     return RESPEC_ERR_HIP;
   }

@@ -8,6 +8,7 @@
 
 namespace respec {
 
+constexpr int kCUs = 256;        // compute units of an MI355X
 constexpr int kMaxNodes = 128;   // tree nodes per sequence (ancestor bitsets of 4 words)
 constexpr int kMaxDepth = 64;    // chain bits fit one 64-bit mask
 constexpr int kVtPad = 4;        // elements of padding per transposed-V row in LDS
@@ -49,7 +50,7 @@ struct LmArgs {
   const void* w;           // [V][Hd]
   float* logits;           // [M][V]
   int32_t m_rows, vocab, hidden_size;
-  int32_t n_mtiles;        // tiles of 16*MB token rows
+  int32_t n_mtiles;        // tiles of lm_tile_rows token rows
   float* partials;         // [M][n_vtiles][4] per-tile row statistics {m, S, T, argmax}, or null
   int32_t n_vtiles;        // vocabulary tiles of 64 rows
 };
@@ -133,9 +134,15 @@ hipError_t launch_attn_merge(int dtype, int head_dim, dim3 grid, const AttnArgs&
 hipError_t launch_tree_attn_stream(int head_dim, int kg, dim3 grid, const AttnArgs& a, hipStream_t s,
                                    hipEvent_t ev_start = nullptr);
 hipError_t set_tree_attn_stream_lds_limit(int head_dim);
-// mb: 16-row token blocks per workgroup (1-4 plain, 8 and 16 GEMM); wide: bf16 with up to 64 token
-// rows in the GEMM kernel's 256-row vocabulary tiles (n_mtiles = 1)
-hipError_t launch_lmhead(int dtype, int mb, bool wide, const LmArgs& a, hipStream_t s, hipEvent_t ev_stop = nullptr);
+// Kernels and tiles of the LM head, token rows x vocabulary rows (64 in the plain kernel)
+enum class LmTile {
+  kPlain16, kPlain32, kPlain48, kPlain64,
+  kGemm64x256, kGemm128x128,
+  kPair192x128, kPair128x256, kPair160x256, kPair192x256, kPair224x256, kPair256x256
+};
+LmTile lm_tile(int dtype, int m_rows, int vocab);
+int lm_tile_rows(LmTile tile);
+hipError_t launch_lmhead(int dtype, LmTile tile, const LmArgs& a, hipStream_t s, hipEvent_t ev_stop = nullptr);
 constexpr int kLmTileRows = 64;  // vocabulary rows per statistics tile (one plain LM-head workgroup)
 // Per-tile partial of the vocabulary statistics of one token row over its tile
 // of 64 vocabulary rows: {m, S, T, argmax}, 16 bytes.  (m, argmax) is also the

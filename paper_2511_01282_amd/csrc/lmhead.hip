@@ -26,6 +26,7 @@
 
 #include "common.hpp"
 #include "kernels.hpp"
+#include "lmhead.hpp"
 
 namespace respec {
 
@@ -365,15 +366,14 @@ __global__ __launch_bounds__(256, 2) void lmhead_persistent_kernel(LmArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// GEMM variant (bf16), fed by DMA, in three tile shapes: MT = 256 token rows
-// by VR = 128 vocabulary rows (129 or more rows in all), MT = 128 by VR = 128
-// (65 to 128 rows), and MT = 64 by VR = 256 (at most 64 rows over a
-// vocabulary of more than two 64-row tiles per CU, where each x row then
-// serves four times as many W rows).  Every byte of W and x a workgroup needs
-// crosses its CU once:
+// GEMM variant (bf16), fed by DMA, in two tile shapes: MT = 128 token rows by
+// VR = 128 vocabulary rows (65 to 128 rows), and MT = 64 by VR = 256 (at most 64
+// rows over a vocabulary of more than two 64-row tiles per CU, where each x row
+// then serves four times as many W rows).  Every byte of W and x a workgroup
+// needs crosses its CU once:
 //   - K advances in 128-byte steps (64 elements); the W and x rows of a step go
 //     straight from memory into an LDS stage by DMA (global_load_lds, 16 bytes
-//     per lane, no registers), in a ring of S = 3 stages (48 or 40 KB): after the
+//     per lane, no registers), in a ring of S = 4 or 3 stages (32 or 40 KB): after the
 //     barrier that publishes step c (every wave has finished step c-1 by then)
 //     step c+2 is requested into c-1's stage, so two steps are in flight while
 //     one is multiplied (the W and x rows of a step share a stage: giving W a
@@ -385,9 +385,7 @@ __global__ __launch_bounds__(256, 2) void lmhead_persistent_kernel(LmArgs a) {
 //     token blocks past the last row are multiplied, not stored):
 //     wave w owns vocabulary rows 64 (w % WV) .. +63 and token rows
 //     MT/WT (w / WV) .. +MT/WT-1, and issues an eighth of every step's DMA
-//     requests (at 256 x 128, four waves in a 2 x 2 grid, each with twice the
-//     products and requests, measured ~6 % slower: the CU's feed from L2 grows
-//     with the number of waves that issue);
+//     requests;
 //   - products on v_mfma_f32_32x32x16_bf16 with W as the A operand (32
 //     vocabulary rows) and x as the B operand (32 token rows); each step's
 //     fragments are requested ahead of its products;
@@ -396,9 +394,6 @@ __global__ __launch_bounds__(256, 2) void lmhead_persistent_kernel(LmArgs a) {
 //   - the logits leave through LDS as a [token row][VR] tile, so that each
 //     token row's 4 VR bytes are stored contiguously, and each thread reduces
 //     one token row of that tile over one 64-row statistics tile.
-constexpr int kGmStep = 128;                    // bytes of a row per K step (64 elements)
-constexpr int kGmWaves = 8;                     // waves per workgroup
-
 template <int MT, int VR>
 struct GmShape {
   static constexpr int WV = VR / 64;                                // vocabulary waves (64 rows each)
@@ -423,26 +418,6 @@ struct GmShape {
   // chunk position of chunk c of stage row r
   static __device__ __forceinline__ int swz(int c, int r) { return c ^ ((r >> 1) & 7); }
 };
-
-// One 1 KB DMA request (8 rows of 128 bytes): lane l fills chunk position l % 8
-// of row 8 q + l / 8 with the chunk that belongs there.
-__device__ __forceinline__ void gm_dma(uint32_t lds_dst, uint64_t base, uint32_t off) {
-  uint32_t saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %1\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %2, %3\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "s"(lds_dst), "v"(off), "s"(base)
-      : "memory");
-}
-
-__device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
-  return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
-         (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
-}
 
 template <int MT, int VR>
 __global__ __launch_bounds__(64 * kGmWaves) void lmhead_gemm_kernel(LmArgs a) {
@@ -595,33 +570,8 @@ __global__ __launch_bounds__(64 * kGmWaves) void lmhead_gemm_kernel(LmArgs a) {
       const int row = u % MT, h = u / MT;
       const int vh = v0 + kLmTileRows * h;
       if (row >= rows || vh >= a.vocab) continue;  // (no statistics tile past V)
-      const unsigned char* zr = tile + row * G::kTileRowB + h * kLmTileRows * 4;
-      float z[kLmTileRows];
-#pragma unroll
-      for (int q = 0; q < kLmTileRows / 4; ++q) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(zr + 16 * q);
-        z[4 * q] = v[0];
-        z[4 * q + 1] = v[1];
-        z[4 * q + 2] = v[2];
-        z[4 * q + 3] = v[3];
-      }
-      const int nv = a.vocab - vh;  // entries at or past V are not logits
-      float mx = kNegInf;
-#pragma unroll
-      for (int i = 0; i < kLmTileRows; ++i) mx = i < nv ? fmaxf(mx, z[i]) : mx;
-      float S = 0.f, T = 0.f;
-      int am = 0x7FFFFFFF;
-#pragma unroll
-      for (int i = kLmTileRows - 1; i >= 0; --i) {
-        const bool ok = i < nv;
-        const float d = z[i] - mx;
-        const float e = ok ? __expf(d) : 0.f;
-        S += e;
-        T += ok ? e * d : 0.f;
-        am = (ok && z[i] == mx) ? vh + i : am;
-      }
-      *reinterpret_cast<u32x4*>(a.partials + ((size_t)(m0 + row) * a.n_vtiles + vh / kLmTileRows) * kTileWords) =
-          u32x4{__float_as_uint(mx), __float_as_uint(S), __float_as_uint(T), (uint32_t)am};
+      tile_row_stats(reinterpret_cast<const f32x4*>(tile + row * G::kTileRowB + h * kLmTileRows * 4), vh, a.vocab,
+                     a.partials + ((size_t)(m0 + row) * a.n_vtiles + vh / kLmTileRows) * kTileWords);
     }
   }
 }
@@ -656,40 +606,85 @@ static hipError_t launch_plain(dim3 grid, const LmArgs& a, hipStream_t s, hipEve
   return launch_k(lmhead_kernel<T, MB>, grid, blk, 0, s, nullptr, ev_stop, a);
 }
 
+// Time of one tile of the shape while every CU runs one, and what it covers (bf16).
+struct TileCost {
+  LmTile tile;
+  int rows, vocab, us;
+};
+
+// Which kernel and tile M token rows take.
+//   - float32, and up to 64 rows in general: W is streamed once and bounds it
+//     (plain kernel, 64 vocabulary rows per workgroup).  bf16 with more 64-row
+//     vocabulary tiles than two per CU: 256-row tiles, so that x crosses the CU a
+//     quarter as often (128256 rows, 64 tokens: 197 against 239 us).
+//   - bf16, 65 rows and more: the tile with the fewest rounds of one tile per CU,
+//     weighted with the time of a round (measured at 4096 columns; every shape's
+//     loop scales with the columns).  Larger tiles do more per byte that crosses
+//     the CU, smaller ones leave less of a last round, or of a last tile, empty.
+//     Measured / second best, us: 32000 rows by 142 tokens 72 / 77 (128 by 256),
+//     by 288 83 / 89, by 512 106 / 136, by 624 155 / 170, by 896 200 / 215;
+//     128256 rows by 128 210 / 218, by 384 390 / 410, by 510 455 / 560.
+LmTile lm_tile(int dtype, int M, int vocab) {
+  const int n_tiles = (vocab + kLmRows - 1) / kLmRows;
+  if (dtype != 1 || M <= 64) {
+    if (dtype == 1 && n_tiles > 2 * kCUs) return LmTile::kGemm64x256;
+    return M <= 16 ? LmTile::kPlain16 : M <= 32 ? LmTile::kPlain32 : M <= 48 ? LmTile::kPlain48 : LmTile::kPlain64;
+  }
+  static constexpr TileCost kCosts[] = {
+      {LmTile::kGemm128x128, 128, 128, 50}, {LmTile::kPair192x128, 192, 128, 62}, {LmTile::kPair128x256, 128, 256, 71},
+      {LmTile::kPair160x256, 160, 256, 78}, {LmTile::kPair192x256, 192, 256, 84}, {LmTile::kPair224x256, 224, 256, 91},
+      {LmTile::kPair256x256, 256, 256, 97}};
+  LmTile best = LmTile::kPair256x256;
+  long long least = -1;
+  for (const TileCost& c : kCosts) {
+    const long long tiles = (long long)((M + c.rows - 1) / c.rows) * ((vocab + c.vocab - 1) / c.vocab);
+    const long long t = (tiles + kCUs - 1) / kCUs * c.us;
+    if (least < 0 || t < least) {
+      least = t;
+      best = c.tile;
+    }
+  }
+  return best;
+}
+
+int lm_tile_rows(LmTile t) {
+  switch (t) {
+    case LmTile::kPlain16: return 16;
+    case LmTile::kPlain32: return 32;
+    case LmTile::kPlain48: return 48;
+    case LmTile::kPlain64: case LmTile::kGemm64x256: return 64;
+    case LmTile::kGemm128x128: case LmTile::kPair128x256: return 128;
+    case LmTile::kPair160x256: return 160;
+    case LmTile::kPair192x128: case LmTile::kPair192x256: return 192;
+    case LmTile::kPair224x256: return 224;
+    default: return 256;
+  }
+}
+
 template <typename T>
-static hipError_t launch_mb(int mb, dim3 grid, const LmArgs& a, hipStream_t s, hipEvent_t ev_stop) {
-  switch (mb) {
-    case 1: return launch_plain<T, 1>(grid, a, s, ev_stop);
-    case 2: return launch_plain<T, 2>(grid, a, s, ev_stop);
-    case 3: return launch_plain<T, 3>(grid, a, s, ev_stop);
-    case 4: return launch_plain<T, 4>(grid, a, s, ev_stop);
+static hipError_t launch_small(LmTile tile, const LmArgs& a, hipStream_t s, hipEvent_t ev_stop) {
+  const int n_vt = (a.vocab + kLmRows - 1) / kLmRows;
+  const dim3 grid((n_vt + 7) / 8 * 8 * a.n_mtiles);
+  switch (tile) {
+    case LmTile::kPlain16: return launch_plain<T, 1>(grid, a, s, ev_stop);
+    case LmTile::kPlain32: return launch_plain<T, 2>(grid, a, s, ev_stop);
+    case LmTile::kPlain48: return launch_plain<T, 3>(grid, a, s, ev_stop);
+    case LmTile::kPlain64: return launch_plain<T, 4>(grid, a, s, ev_stop);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_lmhead(int dtype, int mb, bool wide, const LmArgs& a, hipStream_t s, hipEvent_t ev_stop) {
-  const int n_vt = (a.vocab + kLmRows - 1) / kLmRows;
-  const int n_grp = (n_vt + 7) / 8;
-  dim3 grid(n_grp * 8 * a.n_mtiles);
-  if (mb == 8) {  // GEMM variant: 128 token rows per tile, 128-row vocabulary tiles (bf16)
-    if (dtype != 1 || a.hidden_size % 256 != 0) return hipErrorInvalidValue;
-    const int n_vt2 = (a.vocab + 127) / 128;
-    dim3 tgrid(((n_vt2 + 7) / 8) * 8 * a.n_mtiles);
-    return launch_k(lmhead_gemm_kernel<128, 128>, tgrid, dim3(64 * kGmWaves), 0, s, nullptr, ev_stop, a);
-  }
-  if (mb == 16) {  // GEMM variant: 256 token rows per tile, 128-row vocabulary tiles (bf16)
-    if (dtype != 1 || a.hidden_size % 256 != 0) return hipErrorInvalidValue;
-    const int n_vt2 = (a.vocab + 127) / 128;
-    dim3 tgrid(((n_vt2 + 7) / 8) * 8 * a.n_mtiles);
-    return launch_k(lmhead_gemm_kernel<256, 128>, tgrid, dim3(64 * kGmWaves), 0, s, nullptr, ev_stop, a);
-  }
-  if (wide) {  // GEMM variant: up to 64 token rows, 256-row vocabulary tiles (bf16)
-    if (dtype != 1 || mb > 4 || a.hidden_size % 256 != 0) return hipErrorInvalidValue;
-    const int n_vt2 = (a.vocab + 255) / 256;
-    dim3 tgrid(((n_vt2 + 7) / 8) * 8 * a.n_mtiles);
-    return launch_k(lmhead_gemm_kernel<64, 256>, tgrid, dim3(64 * kGmWaves), 0, s, nullptr, ev_stop, a);
-  }
-  return dtype == 1 ? launch_mb<bf16_t>(mb, grid, a, s, ev_stop) : launch_mb<float>(mb, grid, a, s, ev_stop);
+hipError_t launch_lmhead(int dtype, LmTile tile, const LmArgs& a, hipStream_t s, hipEvent_t ev_stop) {
+  if (tile <= LmTile::kPlain64)
+    return dtype == 1 ? launch_small<bf16_t>(tile, a, s, ev_stop) : launch_small<float>(tile, a, s, ev_stop);
+  if (dtype != 1 || a.hidden_size % 256 != 0) return hipErrorInvalidValue;
+  const dim3 blk(64 * kGmWaves);
+  auto grid = [&](int vr) { return dim3(((a.vocab + vr - 1) / vr + 7) / 8 * 8 * a.n_mtiles); };
+  if (tile == LmTile::kGemm64x256)
+    return launch_k(lmhead_gemm_kernel<64, 256>, grid(256), blk, 0, s, nullptr, ev_stop, a);
+  if (tile == LmTile::kGemm128x128)
+    return launch_k(lmhead_gemm_kernel<128, 128>, grid(128), blk, 0, s, nullptr, ev_stop, a);
+  return launch_lmhead_pair(tile, a, s, ev_stop);
 }
 
 }  // namespace respec
