@@ -53,6 +53,8 @@ struct LmArgs {
   int32_t n_mtiles;        // tiles of lm_tile_rows token rows
   float* partials;         // [M][n_vtiles][4] per-tile row statistics {m, S, T, argmax}, or null
   int32_t n_vtiles;        // vocabulary tiles of 64 rows
+  // DMA-fed kernels of lmhead.hip: tiles of full height, and the height of those after them
+  int32_t full_tiles, tail_rows;
 };
 
 struct VocabArgs {

@@ -368,8 +368,8 @@ __global__ __launch_bounds__(256, 2) void lmhead_persistent_kernel(LmArgs a) {
 // ---------------------------------------------------------------------------
 // GEMM variant (bf16), fed by DMA, in two tile shapes: MT = 128 token rows by
 // VR = 128 vocabulary rows (65 to 128 rows), and MT = 64 by VR = 256 (at most 64
-// rows over a vocabulary of more than two 64-row tiles per CU, where each x row
-// then serves four times as many W rows).  Every byte of W and x a workgroup
+// rows; each x row then serves four times as many W rows as in the plain kernel),
+// the last of them lower (LmArgs::full_tiles).  Every byte of W and x a workgroup
 // needs crosses its CU once:
 //   - K advances in 128-byte steps (64 elements); the W and x rows of a step go
 //     straight from memory into an LDS stage by DMA (global_load_lds, 16 bytes
@@ -433,8 +433,11 @@ __global__ __launch_bounds__(64 * kGmWaves) void lmhead_gemm_kernel(LmArgs a) {
   const int id = blockIdx.x;
   const int grp = id / (8 * n_mt), rem = id % (8 * n_mt);
   const int vt = grp * 8 + rem % 8, mt = rem / 8;  // the M tiles of a vocabulary tile share an XCD
-  if (vt * VR >= a.vocab) return;
-  const int v0 = vt * VR;
+  // vocabulary rows [v0, v1): whole tiles, then lower ones
+  const int v0 = vt < a.full_tiles ? vt * VR : a.full_tiles * VR + (vt - a.full_tiles) * a.tail_rows;
+  if (v0 >= a.vocab) return;
+  const int h = vt < a.full_tiles ? VR : a.tail_rows;
+  const int v1 = min(v0 + h, a.vocab);
   const int m0 = mt * MT;
   const size_t row_bytes = (size_t)a.hidden_size * 2;
   const int n_steps = (int)(row_bytes / kGmStep);  // >= 4 (hidden*2 is a multiple of 512; checked)
@@ -454,11 +457,13 @@ __global__ __launch_bounds__(64 * kGmWaves) void lmhead_gemm_kernel(LmArgs a) {
 #pragma unroll
   for (int j = 0; j < G::kWInst; ++j) {
     const int r = G::RPI * (wave * G::kWInst + j) + lane / G::CPR, pos = lane % G::CPR;
-    const int v = min(v0 + r, a.vocab - 1);
+    const int v = min(v0 + r, v1 - 1);
     wo[j] = (uint32_t)((size_t)(v - v0) * row_bytes + G::swz(pos, r) * 16);
   }
   const uint64_t xbase = reinterpret_cast<uint64_t>(a.x) + (uint64_t)m0 * row_bytes;
   const uint64_t wbase = reinterpret_cast<uint64_t>(a.w) + (uint64_t)v0 * row_bytes;
+  // a low tile's waves past its last row request no W rows (its height is a multiple of a wave's share)
+  const bool w_live = wave * G::kWInst * G::RPI < h;
   auto issue = [&](int c) {  // requests of step c into stage c % S
     const int kc = c + rot < n_steps ? c + rot : c + rot - n_steps;
     const uint64_t ko = (uint64_t)kc * kGmStep;
@@ -467,10 +472,11 @@ __global__ __launch_bounds__(64 * kGmWaves) void lmhead_gemm_kernel(LmArgs a) {
 #pragma unroll
     for (int j = 0; j < G::kXInst; ++j)
       gm_dma(__builtin_amdgcn_readfirstlane(st + (uint32_t)((wave * G::kXInst + j) * 1024)), xb, xo[j]);
+    if (w_live)
 #pragma unroll
-    for (int j = 0; j < G::kWInst; ++j)
-      gm_dma(__builtin_amdgcn_readfirstlane(st + (uint32_t)(MT * kGmStep + (wave * G::kWInst + j) * 1024)), wb,
-             wo[j]);
+      for (int j = 0; j < G::kWInst; ++j)
+        gm_dma(__builtin_amdgcn_readfirstlane(st + (uint32_t)(MT * kGmStep + (wave * G::kWInst + j) * 1024)), wb,
+               wo[j]);
   };
 
   const int wv = wave % G::WV, wt = wave / G::WV;
@@ -492,12 +498,16 @@ __global__ __launch_bounds__(64 * kGmWaves) void lmhead_gemm_kernel(LmArgs a) {
     if (j < n_steps) issue(j);
   for (int c = 0; c < n_steps; ++c) {
     // step c's own requests have landed once at most the newer steps' are pending
-    if (c + G::S - 2 < n_steps)
+    if (c + G::S - 2 < n_steps && !w_live)
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"((G::S - 2) * G::kXInst)
+                   : "memory");
+    else if (c + G::S - 2 < n_steps)
       asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"((G::S - 2) * G::kPerStep)
                    : "memory");
     else
       asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (c + G::S - 1 < n_steps) issue(c + G::S - 1);  // into the stage step c-1 used
+    if (64 * wv >= h) continue;                       // (uniform over the wave) no vocabulary row of its own
     const unsigned char* st = sm + (c % G::S) * G::kStage;
     // (token blocks past the last row are multiplied too: clamped rows, not stored)
     u32x4 af[G::KS][2], bfr[G::KS][G::NT];
@@ -553,12 +563,12 @@ __global__ __launch_bounds__(64 * kGmWaves) void lmhead_gemm_kernel(LmArgs a) {
     for (int row = kRowsPerWave * wave + lane / G::LPR; row < rows; row += kRowsPerWave * kGmWaves) {
       const f32x4 q = *reinterpret_cast<const f32x4*>(tile + row * G::kTileRowB + col * 4);
       float* dst = a.logits + (size_t)(m0 + row) * a.vocab + vv;
-      if (vec_ok && vv + 3 < a.vocab) {
+      if (vec_ok && vv + 3 < v1) {
         *reinterpret_cast<f32x4*>(dst) = q;
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (vv + e < a.vocab) dst[e] = q[e];
+          if (vv + e < v1) dst[e] = q[e];
       }
     }
   }
@@ -569,7 +579,7 @@ __global__ __launch_bounds__(64 * kGmWaves) void lmhead_gemm_kernel(LmArgs a) {
     {
       const int row = u % MT, h = u / MT;
       const int vh = v0 + kLmTileRows * h;
-      if (row >= rows || vh >= a.vocab) continue;  // (no statistics tile past V)
+      if (row >= rows || vh >= v1) continue;  // (no statistics tile past the tile's rows)
       tile_row_stats(reinterpret_cast<const f32x4*>(tile + row * G::kTileRowB + h * kLmTileRows * 4), vh, a.vocab,
                      a.partials + ((size_t)(m0 + row) * a.n_vtiles + vh / kLmTileRows) * kTileWords);
     }
@@ -613,10 +623,14 @@ struct TileCost {
 };
 
 // Which kernel and tile M token rows take.
-//   - float32, and up to 64 rows in general: W is streamed once and bounds it
-//     (plain kernel, 64 vocabulary rows per workgroup).  bf16 with more 64-row
-//     vocabulary tiles than two per CU: 256-row tiles, so that x crosses the CU a
-//     quarter as often (128256 rows, 64 tokens: 197 against 239 us).
+//   - float32, and up to 64 rows over small vocabularies: W is streamed once (plain
+//     kernel, 64 vocabulary rows per workgroup, about two per CU).
+//   - bf16, up to 64 rows, more 64-row vocabulary tiles than CUs: 64 by 256 tiles,
+//     whose x rows cross the CU a quarter as often and whose last round is lower
+//     (launch_lmhead).  Against the plain kernel, 4096 columns, us: 18000 rows by 26
+//     tokens 33 / 40, 24000 by 61 44 / 57, 32000 by 61 51 / 62, 128256 by 64 197 / 239.
+//     Up to 32 tokens and between 1.5 and 2 tiles per CU two plain workgroups per CU
+//     hold the whole vocabulary and are as fast: 32000 by 16 46 / 48.
 //   - bf16, 65 rows and more: the tile with the fewest rounds of one tile per CU,
 //     weighted with the time of a round (measured at 4096 columns; every shape's
 //     loop scales with the columns).  Larger tiles do more per byte that crosses
@@ -627,7 +641,8 @@ struct TileCost {
 LmTile lm_tile(int dtype, int M, int vocab) {
   const int n_tiles = (vocab + kLmRows - 1) / kLmRows;
   if (dtype != 1 || M <= 64) {
-    if (dtype == 1 && n_tiles > 2 * kCUs) return LmTile::kGemm64x256;
+    const bool two_per_cu = M <= 32 && 2 * n_tiles > 3 * kCUs && n_tiles <= 2 * kCUs;
+    if (dtype == 1 && n_tiles > kCUs && !two_per_cu) return LmTile::kGemm64x256;
     return M <= 16 ? LmTile::kPlain16 : M <= 32 ? LmTile::kPlain32 : M <= 48 ? LmTile::kPlain48 : LmTile::kPlain64;
   }
   static constexpr TileCost kCosts[] = {
@@ -679,11 +694,27 @@ hipError_t launch_lmhead(int dtype, LmTile tile, const LmArgs& a, hipStream_t s,
     return dtype == 1 ? launch_small<bf16_t>(tile, a, s, ev_stop) : launch_small<float>(tile, a, s, ev_stop);
   if (dtype != 1 || a.hidden_size % 256 != 0) return hipErrorInvalidValue;
   const dim3 blk(64 * kGmWaves);
-  auto grid = [&](int vr) { return dim3(((a.vocab + vr - 1) / vr + 7) / 8 * 8 * a.n_mtiles); };
-  if (tile == LmTile::kGemm64x256)
-    return launch_k(lmhead_gemm_kernel<64, 256>, grid(256), blk, 0, s, nullptr, ev_stop, a);
-  if (tile == LmTile::kGemm128x128)
-    return launch_k(lmhead_gemm_kernel<128, 128>, grid(128), blk, 0, s, nullptr, ev_stop, a);
+  if (tile == LmTile::kGemm64x256) {
+    // Whole tiles for as many full rounds of one per CU as there are, and what is left in
+    // one round of lower tiles: a last round of whole tiles left most CUs idle (a CU takes
+    // in about 39 GB/s, so some 140 of them are needed to draw the HBM's rate).  4096
+    // columns by 61 tokens, us, whole tiles / this: 70000 rows 139 / 123; 3584 columns,
+    // 152064 rows 222 / 211.
+    LmArgs t = a;
+    const int units = (a.vocab + 63) / 64, rounds = units / (4 * kCUs), left = units - rounds * 4 * kCUs;
+    const int h = (left + kCUs - 1) / kCUs;  // 0..4 units
+    t.full_tiles = rounds * kCUs;
+    t.tail_rows = 64 * h;
+    const int n = t.full_tiles + (h ? (left + h - 1) / h : 0);
+    return launch_k(lmhead_gemm_kernel<64, 256>, dim3((n + 7) / 8 * 8), blk, 0, s, nullptr, ev_stop, t);
+  }
+  if (tile == LmTile::kGemm128x128) {
+    LmArgs t = a;
+    t.full_tiles = (a.vocab + 127) / 128;
+    t.tail_rows = 128;
+    return launch_k(lmhead_gemm_kernel<128, 128>, dim3((t.full_tiles + 7) / 8 * 8 * a.n_mtiles), blk, 0, s, nullptr,
+                    ev_stop, t);
+  }
   return launch_lmhead_pair(tile, a, s, ev_stop);
 }
 
