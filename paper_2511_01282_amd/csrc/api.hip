@@ -191,7 +191,13 @@ StreamGeom stream_geom(const respec_verify_plan* p, int n, int batch) {
   const int rows = n * p->group, rg = cdiv(rows, 32);
   g.n_rowblk = cdiv(rg, 8);
   g.wr = cdiv(rg, g.n_rowblk);
-  g.kg = g.wr <= 2 ? 4 : g.wr <= 4 ? 2 : 1;
+  // Two row waves in two key groups leave more of the ring in flight per pass than in four
+  // (12 sequences of 8 KV heads and 5-10 nodes over 300-3000 rows 24.1 -> 21.4 us, 32 of 32 heads
+  // and 24-48 nodes over 300-1500 rows 114 -> 112 us); one sequence has more of its few tiles
+  // under way in four, and so have 64-column heads, whose tiles are half as large (32 of 32
+  // heads 78 us in four groups, 88 in two).
+  const bool deep = p->s.head_dim == 128 && batch > 1;
+  g.kg = g.wr <= 2 && !deep ? 4 : g.wr <= 4 ? 2 : 1;
   g.part_rows = g.n_rowblk == 1 ? rows : g.wr * 32;
   g.slices = cdiv(batch, kStreamSlice);
   const int heads = p->s.n_kv_heads * g.n_rowblk;
@@ -287,11 +293,16 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
   const int rows = a.max_nodes_in_batch * plan->group;  // query rows per KV head
   hipError_t ae;
   int merge_rows_per_blk;
-  if (plan->es == 2 && rows > 32) {
-    // more than one wave of rows: KV tiles shared through LDS.  Up to 32 rows the
-    // register path's four independent waves per workgroup are as fast or faster:
-    // 26 nodes over 2048 rows of 32 heads 13.5 us against 15.7 us, 96 sequences of
-    // 1-12 nodes over 100-1500 rows 184 us against 196 us.
+  // More than one wave of rows: KV tiles shared through LDS.  Up to 32 rows the register
+  // path's four independent waves per workgroup are as fast or faster: 26 nodes over 2048
+  // rows of 32 heads 13.5 us against 15.7 us, 96 sequences of 1-12 nodes over 100-1500 rows
+  // 184 us against 196 us.  So they are for one sequence and two waves of rows while a CU has
+  // few tiles (its start-up is 3-4 us shorter, the second read of each tile comes from L2):
+  // 34 nodes of 32 heads over 1000 rows 14.0 against 17.0 us, over 4000 21.6 / 22.9, over 8000
+  // (32 tiles per CU) 31.9 / 30.3; 12 nodes on 8 heads of 4 over 4000 rows 11.4 / 15.0.
+  const long long tiles = (long long)cdiv((long long)a.max_kv_len_in_batch + a.max_nodes_in_batch, kKvTile) * s.n_kv_heads;
+  const bool few = a.batch == 1 && rows <= 64 && tiles <= 20ll * kCUs;
+  if (plan->es == 2 && rows > 32 && !few) {
     const StreamGeom ge = stream_geom(plan, a.max_nodes_in_batch, a.batch);
     at.wr = ge.wr;
     at.n_rowblk = ge.n_rowblk;
