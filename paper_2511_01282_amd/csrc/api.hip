@@ -182,21 +182,23 @@ respec_status respec_verify_workspace_init(const respec_verify_plan* plan, void*
 
 namespace {
 
-// Streaming attention of a step whose largest tree has n nodes.
+// Streaming attention of a step whose largest tree has n nodes and longest prefix max_kv rows.
 struct StreamGeom {
   int wr, kg, n_rowblk, part_rows, pieces, slices;
 };
-StreamGeom stream_geom(const respec_verify_plan* p, int n, int batch) {
+StreamGeom stream_geom(const respec_verify_plan* p, int n, int max_kv, int batch) {
   StreamGeom g;
   const int rows = n * p->group, rg = cdiv(rows, 32);
   g.n_rowblk = cdiv(rg, 8);
   g.wr = cdiv(rg, g.n_rowblk);
   // Two row waves in two key groups leave more of the ring in flight per pass than in four
-  // (12 sequences of 8 KV heads and 5-10 nodes over 300-3000 rows 24.1 -> 21.4 us, 32 of 32 heads
-  // and 24-48 nodes over 300-1500 rows 114 -> 112 us); one sequence has more of its few tiles
-  // under way in four, and so have 64-column heads, whose tiles are half as large (32 of 32
-  // heads 78 us in four groups, 88 in two).
-  const bool deep = p->s.head_dim == 128 && batch > 1;
+  // and start and end a segment sooner (12 sequences of 8 KV heads and 5-10 nodes over 300-3000
+  // rows 24.1 -> 21.4 us; 2 of 32 heads over 200 rows 16.1 -> 12.1).  Four where a 64-column
+  // head's tiles, half as large, go by in long streams (32 of 32 heads over 300-1500 rows 78 us
+  // in four groups, 88 in two; 3 over 500-1000 rows, 12 tiles per CU, 18.1 and 16.7), and for one
+  // sequence.
+  const long long tiles = (long long)batch * cdiv((long long)max_kv + n, kKvTile) * p->s.n_kv_heads;
+  const bool deep = batch > 1 && (p->s.head_dim == 128 || tiles <= 12ll * kCUs);
   g.kg = g.wr <= 2 && !deep ? 4 : g.wr <= 4 ? 2 : 1;
   g.part_rows = g.n_rowblk == 1 ? rows : g.wr * 32;
   g.slices = cdiv(batch, kStreamSlice);
@@ -293,6 +295,9 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
   const int rows = a.max_nodes_in_batch * plan->group;  // query rows per KV head
   hipError_t ae;
   int merge_rows_per_blk;
+  // One split per sequence: the attention kernel divides by its sums and writes x itself (96
+  // sequences of 1-12 nodes over 100-1500 rows: the merge of 624 rows' single partials took 15 us).
+  bool direct = false;
   // More than one wave of rows: KV tiles shared through LDS.  Up to 32 rows the register
   // path's four independent waves per workgroup are as fast or faster: 26 nodes over 2048
   // rows of 32 heads 13.5 us against 15.7 us, 96 sequences of 1-12 nodes over 100-1500 rows
@@ -303,7 +308,7 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
   const long long tiles = (long long)cdiv((long long)a.max_kv_len_in_batch + a.max_nodes_in_batch, kKvTile) * s.n_kv_heads;
   const bool few = a.batch == 1 && rows <= 64 && tiles <= 20ll * kCUs;
   if (plan->es == 2 && rows > 32 && !few) {
-    const StreamGeom ge = stream_geom(plan, a.max_nodes_in_batch, a.batch);
+    const StreamGeom ge = stream_geom(plan, a.max_nodes_in_batch, a.max_kv_len_in_batch, a.batch);
     at.wr = ge.wr;
     at.n_rowblk = ge.n_rowblk;
     at.rows_per_wg = ge.wr * 32;
@@ -338,13 +343,14 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
     merge_rows_per_blk = at.rows_per_wg = ge.rows_per_wg;
     at.wr = ge.wr;
     at.wk = ge.wk;
+    direct = !flat && at.nsplit == 1;
     ae = launch_tree_attn(s.dtype, s.head_dim, ge.nb, dim3(at.nsplit, heads, flat ? 1 : a.batch), ge.threads, ge.lds,
-                          at, st, ev ? ev[0] : nullptr);
+                          at, st, ev ? ev[0] : nullptr, ev && direct ? ev[1] : nullptr);
   }
   if (ae != hipSuccess) return RESPEC_ERR_HIP;
   const int merge_rows = 256 / (s.head_dim / 4);
   dim3 mgrid(cdiv(merge_rows_per_blk, merge_rows), a.batch * s.n_kv_heads * at.n_rowblk);
-  if (launch_attn_merge(s.dtype, s.head_dim, mgrid, at, st, ev ? ev[1] : nullptr) != hipSuccess)
+  if (!direct && launch_attn_merge(s.dtype, s.head_dim, mgrid, at, st, ev ? ev[1] : nullptr) != hipSuccess)
     return RESPEC_ERR_HIP;
 
   // ---- LM head ----

@@ -504,22 +504,59 @@ __device__ __forceinline__ void ancestor_bits(const int (&qnode)[NB], int p_lo, 
   }
 }
 
+// Columns d .. d+3 of one query row's output O: the optional copy of O, and x = round(h + O).
+template <typename T>
+__device__ __forceinline__ void store_row(const AttnArgs& a, size_t gi, f32x4 hv, f32x4 o) {
+  if (a.attn_out) *reinterpret_cast<f32x4*>(a.attn_out + gi) = o;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) Elem<T>::store_sum(a.x_out, gi + i, hv[i], o[i]);
+  if (a.x_copy) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) Elem<T>::store_sum(a.x_copy, gi + i, hv[i], o[i]);
+  }
+}
+
+// Where a row block's outputs go when one split holds the whole sequence (no merge follows).
+struct DirectOut {
+  int node0, rows, row_wg, g;  // rows: query rows of the sequence and KV head
+};
+// Partition of the KV rows: splits of each sequence; pieces of the whole batch (FlatTiles); one
+// split per sequence, whose outputs are written here.  (A kernel of its own: as a run-time branch
+// of the first, the output code cost 26 nodes over 2048 rows 2 us.)
+enum class Part { kSplit, kFlat, kWhole };
+
 // The workgroup's unnormalised partial (O, reference max m, sum l) of each of its
-// rows, from the waves' accumulators (after the row-wide sum of l).  With one
+// rows (or, with Direct, the rows' outputs), from the waves' accumulators (after the row-wide sum of l).  With one
 // wave per row group it is stored directly; otherwise the wk waves of a row group
 // combine their (O, m, l) through LDS (s_work, LDS no longer read by any wave).
-template <int D, int NB>
+template <typename T, int D, int NB, bool Direct>
 __device__ __forceinline__ void store_partial(const AttnArgs& a, unsigned char* s_work, const f32x4 (&o)[D / 16][NB],
                                               const float (&m_run)[NB], const float (&l_run)[NB], size_t pbase,
-                                              int wave, int nwaves, int lane) {
+                                              const DirectOut& out, int wave, int nwaves, int lane) {
   constexpr int DB = D / 16;
   constexpr int RB = 16 * NB;
   const int lr = lane & 15, lg = lane >> 4;
   const int wr = wave % a.wr, wk = wave / a.wr;
+  // O = acc / l of row rl, columns 16 db + 4 lg ..
+  auto direct = [&](int rl, int db, f32x4 acc, float l) {
+    const int rr = out.row_wg + rl;
+    if (rr >= out.rows) return;
+    const int node = rr / a.group, h = out.g * a.group + (rr - node * a.group);
+    const size_t gi = (size_t)(out.node0 + node) * a.hidden_size + (size_t)h * D + 16 * db + 4 * lg;
+    f32x4 hv;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) hv[i] = Elem<T>::to_f32(a.hidden, gi + i);
+    store_row<T>(a, gi, hv, acc * (1.f / l));
+  };
   if (a.wk == 1) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       const int rl = wr * RB + 16 * nb + lr;
+      if constexpr (Direct) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) direct(rl, db, o[db][nb], l_run[nb]);
+        continue;
+      }
 #pragma unroll
       for (int db = 0; db < DB; ++db)
         *reinterpret_cast<f32x4*>(a.part_o + (pbase + rl) * D + 16 * db + 4 * lg) = o[db][nb];
@@ -566,9 +603,12 @@ __device__ __forceinline__ void store_partial(const AttnArgs& a, unsigned char* 
 #pragma unroll
         for (int k = 0; k < 4; ++k)
           if (k < a.wk) acc += so[(((wr + a.wr * k) * DB + db) * NB + nb) * 64 + lane] * wgt[k];
-        *reinterpret_cast<f32x4*>(a.part_o + (pbase + rl) * D + 16 * db + 4 * lg) = acc;
+        if constexpr (Direct)
+          direct(rl, db, acc, Ls);
+        else
+          *reinterpret_cast<f32x4*>(a.part_o + (pbase + rl) * D + 16 * db + 4 * lg) = acc;
       }
-      if (wk == 0 && lg == 0) {
+      if (!Direct && wk == 0 && lg == 0) {
         a.part_m[pbase + rl] = M;
         a.part_l[pbase + rl] = Ls;
       }
@@ -603,7 +643,7 @@ __device__ __forceinline__ int flat_piece(int x, int P, int total) {
 
 // One segment of work: KV rows [kv_lo, min(kv_hi, t_rows)) of sequence b, KV
 // head g, row block rb, written to partial slot `slot`.
-template <typename T, int D, int NB>
+template <typename T, int D, int NB, bool Direct>
 __device__ __forceinline__ void attn_segment(const AttnArgs& a, unsigned char* s_work, int b, int g, int rb,
                                              int kv_lo, int kv_hi_req, int slot) {
   constexpr int ES = Elem<T>::kBytes;
@@ -764,15 +804,15 @@ __device__ __forceinline__ void attn_segment(const AttnArgs& a, unsigned char* s
   // ---- workgroup partial: (O unnormalised, max, sum) per row ----
   const int bgr = (b * a.n_kv_heads + g) * a.n_rowblk + rb;
   const size_t pbase = ((size_t)bgr * a.nsplit + split) * a.rows_per_wg;
-  store_partial<D, NB>(a, s_work, o, m_run, l_run, pbase, wave, nwaves, lane);
+  store_partial<T, D, NB, Direct>(a, s_work, o, m_run, l_run, pbase, DirectOut{node0, R, row_wg, g}, wave, nwaves, lane);
 }
 
-template <typename T, int D, int NB, bool Flat>
+template <typename T, int D, int NB, Part P>
 __global__ __launch_bounds__(256) void tree_attn_kernel(AttnArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int g = blockIdx.y / a.n_rowblk, rb = blockIdx.y % a.n_rowblk;
-  if constexpr (!Flat) {
-    attn_segment<T, D, NB>(a, smem, blockIdx.z, g, rb, blockIdx.x * a.chunk, blockIdx.x * a.chunk + a.chunk,
+  if constexpr (P != Part::kFlat) {
+    attn_segment<T, D, NB, P == Part::kWhole>(a, smem, blockIdx.z, g, rb, blockIdx.x * a.chunk, blockIdx.x * a.chunk + a.chunk,
                            blockIdx.x);
     return;
   }
@@ -781,9 +821,9 @@ __global__ __launch_bounds__(256) void tree_attn_kernel(AttnArgs a) {
   // whatever the lengths; a piece runs one segment per sequence it touches.
   const int lane = threadIdx.x & 63;
   const FlatTiles ft = flat_tiles(a, lane);
-  const int P = a.flat, p = blockIdx.x;
+  const int n_pieces = a.flat, p = blockIdx.x;
   if (ft.total == 0) return;
-  const int T0 = (int)((long long)p * ft.total / P), T1 = (int)((long long)(p + 1) * ft.total / P);
+  const int T0 = (int)((long long)p * ft.total / n_pieces), T1 = (int)((long long)(p + 1) * ft.total / n_pieces);
   const bool touches = lane < a.batch && ft.tiles > 0 && ft.pre < T1 && ft.pre + ft.tiles > T0;
   uint64_t seqs = __ballot(touches);
   bool first = true;
@@ -792,10 +832,10 @@ __global__ __launch_bounds__(256) void tree_attn_kernel(AttnArgs a) {
     seqs &= seqs - 1;
     const int pre = __shfl(ft.pre, b, 64), nt = __shfl(ft.tiles, b, 64);
     const int lo = max(T0, pre) - pre, hi = min(T1, pre + nt) - pre;
-    const int slot = p - flat_piece(pre, P, ft.total);
+    const int slot = p - flat_piece(pre, n_pieces, ft.total);
     if (!first) __syncthreads();  // the previous segment's merge is done with the LDS
     first = false;
-    attn_segment<T, D, NB>(a, smem, b, g, rb, lo * kKvTile, hi * kKvTile, slot);
+    attn_segment<T, D, NB, false>(a, smem, b, g, rb, lo * kKvTile, hi * kKvTile, slot);
   }
 }
 
@@ -876,45 +916,35 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   }
   const float inv = 1.f / Ls;
   acc *= inv;
-  if (a.attn_out) *reinterpret_cast<f32x4*>(a.attn_out + gi) = acc;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) Elem<T>::store_sum(a.x_out, gi + i, hv[i], acc[i]);
-  if (a.x_copy) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) Elem<T>::store_sum(a.x_copy, gi + i, hv[i], acc[i]);
-  }
+  store_row<T>(a, gi, hv, acc);
 }
 
 template <typename T, int D>
 static hipError_t launch_nb(int nb, dim3 grid, int threads, size_t lds, const AttnArgs& a, hipStream_t s,
-                            hipEvent_t ev_start) {
-  const bool flat = a.flat > 0;
-  switch (nb) {
-    case 1:
-      return flat ? launch_k(tree_attn_kernel<T, D, 1, true>, grid, dim3(threads), lds, s, ev_start, nullptr, a)
-                  : launch_k(tree_attn_kernel<T, D, 1, false>, grid, dim3(threads), lds, s, ev_start, nullptr, a);
-    case 2:
-      return flat ? launch_k(tree_attn_kernel<T, D, 2, true>, grid, dim3(threads), lds, s, ev_start, nullptr, a)
-                  : launch_k(tree_attn_kernel<T, D, 2, false>, grid, dim3(threads), lds, s, ev_start, nullptr, a);
-    default: return hipErrorInvalidValue;
-  }
+                            hipEvent_t ev_start, hipEvent_t ev_stop) {
+  auto go = [&](auto kernel) { return launch_k(kernel, grid, dim3(threads), lds, s, ev_start, ev_stop, a); };
+  const Part part = a.flat > 0 ? Part::kFlat : a.nsplit == 1 ? Part::kWhole : Part::kSplit;
+  if (nb == 1)
+    return part == Part::kFlat    ? go(tree_attn_kernel<T, D, 1, Part::kFlat>)
+           : part == Part::kWhole ? go(tree_attn_kernel<T, D, 1, Part::kWhole>)
+                                  : go(tree_attn_kernel<T, D, 1, Part::kSplit>);
+  if (nb == 2)
+    return part == Part::kFlat    ? go(tree_attn_kernel<T, D, 2, Part::kFlat>)
+           : part == Part::kWhole ? go(tree_attn_kernel<T, D, 2, Part::kWhole>)
+                                  : go(tree_attn_kernel<T, D, 2, Part::kSplit>);
+  return hipErrorInvalidValue;
 }
 
 template <typename T, int D>
 static hipError_t set_lds_nb(int nb, size_t lds) {
-  const void* f[2] = {nullptr, nullptr};
-  switch (nb) {
-    case 1:
-      f[0] = reinterpret_cast<const void*>(&tree_attn_kernel<T, D, 1, false>);
-      f[1] = reinterpret_cast<const void*>(&tree_attn_kernel<T, D, 1, true>);
-      break;
-    case 2:
-      f[0] = reinterpret_cast<const void*>(&tree_attn_kernel<T, D, 2, false>);
-      f[1] = reinterpret_cast<const void*>(&tree_attn_kernel<T, D, 2, true>);
-      break;
-    default: return hipErrorInvalidValue;
-  }
-  for (const void* k : f) {
+  if (nb != 1 && nb != 2) return hipErrorInvalidValue;
+  const void* f1[3] = {reinterpret_cast<const void*>(&tree_attn_kernel<T, D, 1, Part::kSplit>),
+                       reinterpret_cast<const void*>(&tree_attn_kernel<T, D, 1, Part::kFlat>),
+                       reinterpret_cast<const void*>(&tree_attn_kernel<T, D, 1, Part::kWhole>)};
+  const void* f2[3] = {reinterpret_cast<const void*>(&tree_attn_kernel<T, D, 2, Part::kSplit>),
+                       reinterpret_cast<const void*>(&tree_attn_kernel<T, D, 2, Part::kFlat>),
+                       reinterpret_cast<const void*>(&tree_attn_kernel<T, D, 2, Part::kWhole>)};
+  for (const void* k : nb == 1 ? f1 : f2) {
     const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
@@ -922,11 +952,11 @@ static hipError_t set_lds_nb(int nb, size_t lds) {
 }
 
 hipError_t launch_tree_attn(int dtype, int head_dim, int nb, dim3 grid, int threads, size_t lds,
-                            const AttnArgs& a, hipStream_t s, hipEvent_t ev_start) {
-  if (dtype == 1 && head_dim == 128) return launch_nb<bf16_t, 128>(nb, grid, threads, lds, a, s, ev_start);
-  if (dtype == 1 && head_dim == 64) return launch_nb<bf16_t, 64>(nb, grid, threads, lds, a, s, ev_start);
-  if (dtype == 0 && head_dim == 128) return launch_nb<float, 128>(nb, grid, threads, lds, a, s, ev_start);
-  if (dtype == 0 && head_dim == 64) return launch_nb<float, 64>(nb, grid, threads, lds, a, s, ev_start);
+                            const AttnArgs& a, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  if (dtype == 1 && head_dim == 128) return launch_nb<bf16_t, 128>(nb, grid, threads, lds, a, s, ev_start, ev_stop);
+  if (dtype == 1 && head_dim == 64) return launch_nb<bf16_t, 64>(nb, grid, threads, lds, a, s, ev_start, ev_stop);
+  if (dtype == 0 && head_dim == 128) return launch_nb<float, 128>(nb, grid, threads, lds, a, s, ev_start, ev_stop);
+  if (dtype == 0 && head_dim == 64) return launch_nb<float, 64>(nb, grid, threads, lds, a, s, ev_start, ev_stop);
   return hipErrorInvalidValue;
 }
 

@@ -127,7 +127,8 @@ inline hipError_t launch_k(F kernel, dim3 grid, dim3 block, size_t lds, hipStrea
 // dtype-dispatching launchers (0 = f32, 1 = bf16); return hipSuccess or the launch error.
 // ev_start / ev_stop: optional timing events (see launch_k).
 hipError_t launch_tree_attn(int dtype, int head_dim, int nb, dim3 grid, int threads, size_t lds,
-                            const AttnArgs& a, hipStream_t s, hipEvent_t ev_start = nullptr);
+                            const AttnArgs& a, hipStream_t s, hipEvent_t ev_start = nullptr,
+                            hipEvent_t ev_stop = nullptr);  // (ev_stop: nsplit == 1, no merge follows)
 hipError_t set_tree_attn_lds_limit(int dtype, int head_dim, int nb, size_t lds);
 hipError_t launch_attn_merge(int dtype, int head_dim, dim3 grid, const AttnArgs& a, hipStream_t s,
                              hipEvent_t ev_stop = nullptr);
