@@ -23,7 +23,8 @@
 //     from LDS instead of loading it once each);
 //   - waves of a row group are merged in LDS; each workgroup writes an
 //     unnormalised partial (O, max, sum) per row;
-//   - a second, wide kernel merges the splits of every row and writes O and
+//   - a second, wide kernel (none where one split holds each sequence: Part::kWhole)
+//     merges the splits of every row and writes O and
 //     x = round(h + O) (one workgroup alone cannot pull the partials of a
 //     head fast enough: a single CU's memory parallelism caps it at tens of
 //     GB/s).
