@@ -314,6 +314,7 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
     at.rows_per_wg = ge.wr * 32;
     merge_rows_per_blk = at.part_rows = ge.part_rows;
     at.pieces = ge.pieces;
+    at.piece_shift = ge.kg == 4 ? 2 : 1;  // a piece holds at least a tile per key group, and two
     at.part_blocks = ge.slices * (ge.pieces - 1) + a.batch;
     at.span = reinterpret_cast<int32_t*>(ws + plan->off_span);
     ae = launch_tree_attn_stream(s.head_dim, ge.kg, dim3(ge.pieces, s.n_kv_heads * ge.n_rowblk, ge.slices), at, st,
@@ -348,9 +349,13 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
                           at, st, ev ? ev[0] : nullptr, ev && direct ? ev[1] : nullptr);
   }
   if (ae != hipSuccess) return RESPEC_ERR_HIP;
-  const int merge_rows = 256 / (s.head_dim / 4);
-  dim3 mgrid(cdiv(merge_rows_per_blk, merge_rows), a.batch * s.n_kv_heads * at.n_rowblk);
-  if (!direct && launch_attn_merge(s.dtype, s.head_dim, mgrid, at, st, ev ? ev[1] : nullptr) != hipSuccess)
+  // partials of a row: its sequence's splits, or of a batch that is cut into pieces about its share of them
+  const long long t_tiles = cdiv((long long)a.max_kv_len_in_batch + a.max_nodes_in_batch, kKvTile);
+  const int splits = at.pieces   ? (int)min((long long)cdiv(at.pieces, a.batch), max(1ll, t_tiles >> at.piece_shift))
+                     : at.flat ? cdiv(at.flat, a.batch)
+                               : at.nsplit;
+  if (!direct && launch_attn_merge(s.dtype, s.head_dim, at, merge_rows_per_blk, splits, st, ev ? ev[1] : nullptr) !=
+                     hipSuccess)
     return RESPEC_ERR_HIP;
 
   // ---- LM head ----

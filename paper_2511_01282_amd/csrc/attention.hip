@@ -844,28 +844,38 @@ __global__ __launch_bounds__(256) void tree_attn_kernel(AttnArgs a) {
 // streaming kernel's.  (One kernel each: as run-time branches, 26 nodes over 2048 rows 82.4 against
 // 81.9 us per step.)
 enum class Merge { kSplits, kFlat, kStream };
+constexpr int kMergeBatch = 8;  // splits whose partials a thread of the merge requests at once
 
 // Split merge and residual: one workgroup per (sequence, KV head, row block,
-// chunk of 256 / (D/4) rows); each thread owns one (row, 4-column) item and
-// requests the partials, maxima and sums of 8 splits at a time.
+// chunk of 256 / (D/4) / G rows); each thread owns one (row, 4-column) item of
+// every G-th batch of 8 splits and requests the partials, maxima and sums of a
+// batch at a time.
 //   w_s = 2^(m_s - M) / sum_s' l_s' 2^(m_s' - M),  M = max_s m_s;
 //   O = sum_s w_s O_s;  x = round(h + O).
 // The partials come from the attention kernel that ran before it on the same
 // stream, so plain loads see them.
-template <typename T, int D, Merge M_>
+//
+// What bounds it: the latency of a batch, 1.1 us, times the batches that a thread takes one
+// after the other.  Above two of them, G = 4 waves share a row's batches and wave 0 adds up
+// their sums through LDS: 63 splits of 119 rows on 4 KV heads 11.0 -> 5.4 us, 32 of 256 rows
+// on 8 heads 9.9 -> 8.9.  (9 to 16 splits: 400 rows on 8 heads over 4000 rows of KV 34.7 us per
+// step with G = 4 and 33.2 with G = 1, few rows the same.)
+template <typename T, int D, Merge M_, int G>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   constexpr int D4 = D / 4;
-  constexpr int kRows = 256 / D4;   // rows per workgroup
-  constexpr int kBatch = 8;         // splits requested per batch
+  constexpr int kItems = 256 / G;       // (row, 4-column) items of a workgroup
+  constexpr int kRows = kItems / D4;    // rows per workgroup
+  constexpr int kBatch = kMergeBatch;   // splits requested per batch
+  static_assert(G == 1 || kItems == 64, "a wave per group");
   const int bgr = blockIdx.y;
   const int rb = bgr % a.n_rowblk, g = (bgr / a.n_rowblk) % a.n_kv_heads, b = bgr / (a.n_rowblk * a.n_kv_heads);
-  const int node0 = a.node_off[b], node1 = a.node_off[b + 1];
-  int n_nodes = node1 - node0;
-  if (node0 < 0 || node1 > a.total_nodes || n_nodes < 1 || n_nodes > a.max_nodes) n_nodes = 0;
-  const int R = n_nodes * a.group;
+  const SeqRows sr = seq_rows(a, b);
+  const int node0 = sr.node0;
+  const int R = sr.n_nodes * a.group;
   const int row_wg = rb * a.rows_per_wg;
-  const int rl = blockIdx.x * kRows + (int)threadIdx.x / D4;  // row within the row block
-  const int d = ((int)threadIdx.x % D4) * 4;
+  const int item = (int)threadIdx.x % kItems, grp = (int)threadIdx.x / kItems;
+  const int rl = blockIdx.x * kRows + item / D4;  // row within the row block
+  const int d = (item % D4) * 4;
   // partials of this sequence: every split, or the pieces its tiles span (flat partition)
   int nsp = a.nsplit;
   if constexpr (M_ == Merge::kFlat) {
@@ -873,7 +883,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     const int pre = __shfl(ft.pre, b, 64), nt = __shfl(ft.tiles, b, 64);
     nsp = nt > 0 ? flat_piece(pre + nt - 1, a.flat, ft.total) - flat_piece(pre, a.flat, ft.total) + 1 : 0;
   }
-  if (rl >= a.rows_per_wg || row_wg + rl >= R) return;
+  if (rl >= a.rows_per_wg || row_wg + rl >= R) return;  // (the same rows in every group)
   size_t sbase = (size_t)bgr * a.nsplit * a.rows_per_wg + rl;
   size_t sstride = (size_t)a.rows_per_wg;
   if constexpr (M_ == Merge::kStream) {  // partial blocks numbered piece + sequence
@@ -893,7 +903,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 
   float M = kNegInf, Ls = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int sp0 = 0; sp0 < nsp; sp0 += kBatch) {
+  for (int sp0 = grp * kBatch; sp0 < nsp; sp0 += G * kBatch) {
     float mv[kBatch], lv[kBatch];
     f32x4 ov[kBatch];
 #pragma unroll
@@ -919,6 +929,32 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
       Ls += lv[u] * e;
     }
     M = Mb;
+  }
+  if constexpr (G > 1) {
+    __shared__ f32x4 s_o[G - 1][kItems];
+    __shared__ float2 s_ml[G - 1][kItems];
+    if (grp > 0) {
+      s_o[grp - 1][item] = acc;
+      s_ml[grp - 1][item] = make_float2(M, Ls);
+    }
+    __syncthreads();
+    if (grp > 0) return;
+    float2 ml[G - 1];
+    float Mb = M;
+#pragma unroll
+    for (int k = 0; k < G - 1; ++k) {
+      ml[k] = s_ml[k][item];
+      Mb = fmaxf(Mb, ml[k].x);
+    }
+    const float keep = M == kNegInf ? 0.f : __builtin_amdgcn_exp2f(M - Mb);
+    acc *= keep;
+    Ls *= keep;
+#pragma unroll
+    for (int k = 0; k < G - 1; ++k) {
+      const float e = ml[k].x == kNegInf ? 0.f : __builtin_amdgcn_exp2f(ml[k].x - Mb);
+      acc += s_o[k][item] * e;
+      Ls += ml[k].y * e;
+    }
   }
   const float inv = 1.f / Ls;
   acc *= inv;
@@ -966,18 +1002,25 @@ hipError_t launch_tree_attn(int dtype, int head_dim, int nb, dim3 grid, int thre
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_attn_merge(int dtype, int head_dim, dim3 grid, const AttnArgs& a, hipStream_t s,
+template <typename T, int D, int G>
+static hipError_t launch_merge(const AttnArgs& a, int rows_per_blk, hipStream_t s, hipEvent_t ev_stop) {
+  const int rows = 256 / (D / 4) / G;
+  const dim3 grid((rows_per_blk + rows - 1) / rows, a.batch * a.n_kv_heads * a.n_rowblk), blk(256);
+  auto go = [&](auto kernel) { return launch_k(kernel, grid, blk, 0, s, nullptr, ev_stop, a); };
+  return a.pieces ? go(attn_merge_kernel<T, D, Merge::kStream, G>)
+         : a.flat ? go(attn_merge_kernel<T, D, Merge::kFlat, G>)
+                  : go(attn_merge_kernel<T, D, Merge::kSplits, G>);
+}
+
+hipError_t launch_attn_merge(int dtype, int head_dim, const AttnArgs& a, int rows_per_blk, int splits, hipStream_t s,
                              hipEvent_t ev_stop) {
-  const dim3 blk(256);
-  auto go = [&](auto splits, auto flat, auto stream) {
-    return launch_k(a.pieces ? stream : a.flat ? flat : splits, grid, blk, 0, s, nullptr, ev_stop, a);
-  };
+  const bool wide = splits > 2 * kMergeBatch;
 #define RESPEC_MERGE(T, D) \
-  go(attn_merge_kernel<T, D, Merge::kSplits>, attn_merge_kernel<T, D, Merge::kFlat>, attn_merge_kernel<T, D, Merge::kStream>)
-  if (dtype == 1 && head_dim == 128) return RESPEC_MERGE(bf16_t, 128);
-  if (dtype == 1 && head_dim == 64) return RESPEC_MERGE(bf16_t, 64);
-  if (dtype == 0 && head_dim == 128) return RESPEC_MERGE(float, 128);
-  if (dtype == 0 && head_dim == 64) return RESPEC_MERGE(float, 64);
+  return wide ? launch_merge<T, D, 4>(a, rows_per_blk, s, ev_stop) : launch_merge<T, D, 1>(a, rows_per_blk, s, ev_stop)
+  if (dtype == 1 && head_dim == 128) RESPEC_MERGE(bf16_t, 128);
+  if (dtype == 1 && head_dim == 64) RESPEC_MERGE(bf16_t, 64);
+  if (dtype == 0 && head_dim == 128) RESPEC_MERGE(float, 128);
+  if (dtype == 0 && head_dim == 64) RESPEC_MERGE(float, 64);
 #undef RESPEC_MERGE
   return hipErrorInvalidValue;
 }

@@ -218,7 +218,7 @@ __global__ __launch_bounds__(512) void tree_attn_stream_kernel(AttnArgs a) {
     const int rows = sr.n_nodes * a.group - row_wg;
     if (rows <= 0) return;
     const int tiles = (sr.L + sr.n_nodes + kKvTile - 1) / kKvTile;
-    const int P = min(a.pieces, max(1, tiles >> (KG == 4 ? 2 : KG == 2 ? 1 : 0)));
+    const int P = min(a.pieces, max(1, tiles >> a.piece_shift));
     if (p >= P) return;
     const int q = tiles / P, r = tiles - q * P;
     const int lo = p * q + p * r / P, hi_t = (p + 1) * q + (p + 1) * r / P;

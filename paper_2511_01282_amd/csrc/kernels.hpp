@@ -38,8 +38,9 @@ struct AttnArgs {
   // streaming kernel (bf16): pieces per (KV head, row block) and slice of sequences; a segment's
   // partial block is slice * (pieces - 1) + piece + sequence, of part_blocks per (head, row block),
   // each part_rows rows; span [B][Hkv][n_rowblk][2]: first and last piece of each sequence.
-  // pieces == 0: the partials of tree_attn_kernel.
-  int32_t pieces, part_blocks, part_rows;
+  // pieces == 0: the partials of tree_attn_kernel.  One sequence has min(pieces, tiles >> piece_shift)
+  // pieces (at least one).
+  int32_t pieces, part_blocks, part_rows, piece_shift;
   int32_t* span;
 };
 
@@ -130,7 +131,9 @@ hipError_t launch_tree_attn(int dtype, int head_dim, int nb, dim3 grid, int thre
                             const AttnArgs& a, hipStream_t s, hipEvent_t ev_start = nullptr,
                             hipEvent_t ev_stop = nullptr);  // (ev_stop: nsplit == 1, no merge follows)
 hipError_t set_tree_attn_lds_limit(int dtype, int head_dim, int nb, size_t lds);
-hipError_t launch_attn_merge(int dtype, int head_dim, dim3 grid, const AttnArgs& a, hipStream_t s,
+// rows_per_blk: rows of a row block that can be live; splits: partials of a row (an estimate where the
+// device's lengths decide)
+hipError_t launch_attn_merge(int dtype, int head_dim, const AttnArgs& a, int rows_per_blk, int splits, hipStream_t s,
                              hipEvent_t ev_stop = nullptr);
 // bf16 streaming kernel: a.wr row waves (1..8) of 32 query rows in each of kg key groups
 // (4 for wr <= 2, 2 for wr <= 4, 1), grid (pieces, Hkv * n_rowblk, slices of kStreamSlice sequences)
