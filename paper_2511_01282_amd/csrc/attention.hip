@@ -887,8 +887,13 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   size_t sbase = (size_t)bgr * a.nsplit * a.rows_per_wg + rl;
   size_t sstride = (size_t)a.rows_per_wg;
   if constexpr (M_ == Merge::kStream) {  // partial blocks numbered piece + sequence
-    const int first = a.span[2 * (size_t)bgr];
-    nsp = a.span[2 * (size_t)bgr + 1] - first + 1;
+    int first = 0;
+    if (a.batch == 1) {  // one sequence's pieces, without a word from the attention kernel to wait for
+      nsp = stream_pieces_of_one(a, (sr.L + sr.n_nodes + kKvTile - 1) / kKvTile);
+    } else {
+      first = a.span[2 * (size_t)bgr];
+      nsp = a.span[2 * (size_t)bgr + 1] - first + 1;
+    }
     sstride = (size_t)a.part_rows;
     sbase = ((size_t)(g * a.n_rowblk + rb) * a.part_blocks + b / kStreamSlice * (a.pieces - 1) + first + b) * sstride + rl;
   }

@@ -21,4 +21,9 @@ __device__ __forceinline__ SeqRows seq_rows(const AttnArgs& a, int b) {
   return SeqRows{node0, n_nodes, n_nodes > 0 ? L : 0};
 }
 
+// Pieces of the streaming kernel's only sequence (of `tiles` KV tiles).
+__device__ __forceinline__ int stream_pieces_of_one(const AttnArgs& a, int tiles) {
+  return min(a.pieces, max(1, tiles >> a.piece_shift));
+}
+
 }  // namespace respec

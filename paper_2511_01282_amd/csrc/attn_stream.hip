@@ -218,15 +218,13 @@ __global__ __launch_bounds__(512) void tree_attn_stream_kernel(AttnArgs a) {
     const int rows = sr.n_nodes * a.group - row_wg;
     if (rows <= 0) return;
     const int tiles = (sr.L + sr.n_nodes + kKvTile - 1) / kKvTile;
-    const int P = min(a.pieces, max(1, tiles >> a.piece_shift));
+    const int P = stream_pieces_of_one(a, tiles);
     if (p >= P) return;
     const int q = tiles / P, r = tiles - q * P;
     const int lo = p * q + p * r / P, hi_t = (p + 1) * q + (p + 1) * r / P;
     if (lane == 0) {  // (every wave writes the same words)
       segs[0] = Seg{0, sr.node0, sr.n_nodes, sr.L, lo, hi_t, tiles, 0};
       ctl[0] = 1;
-      if (wave == 0 && lo == 0) span_of(0)[0] = p;
-      if (wave == 0 && hi_t == tiles) span_of(0)[1] = p;
     }
     wave_lds_sync();
   } else {

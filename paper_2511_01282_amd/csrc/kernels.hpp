@@ -39,7 +39,7 @@ struct AttnArgs {
   // partial block is slice * (pieces - 1) + piece + sequence, of part_blocks per (head, row block),
   // each part_rows rows; span [B][Hkv][n_rowblk][2]: first and last piece of each sequence.
   // pieces == 0: the partials of tree_attn_kernel.  One sequence has min(pieces, tiles >> piece_shift)
-  // pieces (at least one).
+  // pieces (at least one), and no span.
   int32_t pieces, part_blocks, part_rows, piece_shift;
   int32_t* span;
 };
