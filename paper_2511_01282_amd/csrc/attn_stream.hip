@@ -27,6 +27,13 @@
 // Waves.  wr row waves own 32 query rows each, (node, head-in-group) pairs; KG
 // key groups of wr waves take the tiles of a pass in turn, and at a segment's
 // end hand their (m, l, O) to group 0 through the slots of the last pass.
+// A pass of four tiles with one or two key groups: the barriers are half as
+// many as with one tile per group, and the waves of a SIMD drift apart inside
+// a pass by themselves (65 nodes of 32 heads, attention layer over 16384 rows:
+// 66.0 us with one tile per group, 63.6 with two; 32 heads of 64 columns 47.2
+// and 41.6).  Holding waves 4-7 half a tile behind instead costs registers and
+// gains nothing: 12 sequences of 24-61 nodes on 8 heads of 4 over 500-16000
+// rows 121.0 with it, 114.5 without.
 //
 // What bounds it: with 8 row waves (256 rows) the arithmetic of two waves per
 // SIMD, 1.3 us per tile of which the matrix products are 0.7 (a DMA-less copy
@@ -431,11 +438,6 @@ __global__ __launch_bounds__(512) void tree_attn_stream_kernel(AttnArgs a) {
     const int s = s_cur + q;
     return s >= S ? s - S : s;
   };
-  // Waves w and w + 4 share a SIMD.  The upper ones run half a tile behind:
-  // they meet a pass's barrier between the scores and the softmax of their
-  // previous tile, so that one wave's matrix products run under the other's
-  // softmax (a pass would otherwise start both in the same phase).
-  const bool late = wave >= 4;
 
   for (int sg = 0; sg < n_seg; ++sg) {
     const int b = seg_word(sg, 0), n_nodes = seg_word(sg, 2), L = seg_word(sg, 3), lo = seg_word(sg, 4),
@@ -469,17 +471,14 @@ __global__ __launch_bounds__(512) void tree_attn_stream_kernel(AttnArgs a) {
     const int rem = n_t % TP, rot = rot_of(n_t);
     int c = rem ? rem : TP;
     for (int j = 0; j < n_t; j += c, c = TP) {
-      if (!late || j == 0) begin_pass(c);
+      begin_pass(c);
 #pragma unroll
       for (int u = 0; u < TPG; ++u) {
         const int t = j + KG * u + grp;
-        const bool mine = KG * u + grp < c && live;
-        f32x16 s;
-        u32x4 vf[DB][2];
-        if (mine) {
+        if (KG * u + grp < c && live) {
           const unsigned char* kt = smem + slot_of(KG * u + grp) * G::kSlot;
           // S^T = K Q^T: lane holds, of query row r32, keys 8 (i / 4) + 4 hi + i % 4
-          s = f32x16{};
+          f32x16 s = f32x16{};
           {
             const unsigned char* kr = kt + r32 * D * 2;
             u32x4 kf[KS];
@@ -492,6 +491,7 @@ __global__ __launch_bounds__(512) void tree_attn_stream_kernel(AttnArgs a) {
           // V^T fragments: A operand rows d = 32 db + (lane & 31), keys 16 k2 + {0..3, 8..11} + 4 hi, by
           // transposing reads (lane j of a 16-lane group addresses row + j / 4, columns 4 (j % 4) ..
           // and receives column j of the four rows)
+          u32x4 vf[DB][2];
           {
             typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
             typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
@@ -512,9 +512,6 @@ __global__ __launch_bounds__(512) void tree_attn_stream_kernel(AttnArgs a) {
               }
             }
           }
-        }
-        if (late && u == TPG - 1 && j + c < n_t) begin_pass(TP);
-        if (mine) {
           const int t0 = tile_row(lo, n_t, rot, t);
           if (t0 + kKvTile > L) {  // tree rows (or the end of the sequence) in this tile
 #pragma unroll
@@ -666,13 +663,13 @@ hipError_t go(bool launch, dim3 grid, int threads, const AttnArgs& a, hipStream_
 template <int D>
 hipError_t go_kg(int kg, bool launch, dim3 grid, int threads, const AttnArgs& a, hipStream_t s, hipEvent_t ev_start) {
   switch (kg) {
-    case 1: return go<D, 9, 1, 3, 4>(launch, grid, threads, a, s, ev_start);
+    case 1: return go<D, 9, 1, 4, 4>(launch, grid, threads, a, s, ev_start);
     case 2:
       if (!launch || threads < 256) {
-        const hipError_t e = go<D, 9, 2, 1, 2>(launch, grid, threads, a, s, ev_start);
+        const hipError_t e = go<D, 9, 2, 2, 2>(launch, grid, threads, a, s, ev_start);
         if (launch || e != hipSuccess) return e;
       }
-      return go<D, 9, 2, 1, 4>(launch, grid, threads, a, s, ev_start);
+      return go<D, 9, 2, 2, 4>(launch, grid, threads, a, s, ev_start);
     case 4: return go<D, 9, 4, 1, 4>(launch, grid, threads, a, s, ev_start);
     default: return hipErrorInvalidValue;
   }
