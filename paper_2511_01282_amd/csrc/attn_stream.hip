@@ -301,9 +301,14 @@ __global__ __launch_bounds__(512) void tree_attn_stream_kernel(AttnArgs a) {
   // A segment's tiles are taken in rotated order, from a start that differs from
   // workgroup to workgroup: heads and pieces lie at regular distances, and
   // workgroups that all walk their tiles from the first one meet on the same
-  // memory channels (DMA ring alone, 65 queries of 32 heads over 16384 rows in
-  // a cache of 16512: 54 us in order, 46 us rotated).
-  auto rot_of = [&](int n_t) { return (int)((blockIdx.x * 5 + blockIdx.y * 3) % (uint32_t)n_t); };
+  // memory channels where a head's rows take near a multiple of 2 MB plus or minus
+  // 32 KB.  The start is quadratic in the head: one that is linear (or none) moves
+  // the meeting to other cache capacities.  33 nodes of 32 heads over 15800 rows, us per
+  // attention layer at 50 capacities of 15872 to 16656 rows: by 5 x alone 55.4-69.3, by
+  // 5 x + 3 y 55.7-68.4, by 5 x + 17 y 55.0-61.5, this 56.0-58.4 (KV tiles in order, in a
+  // kernel of per-sequence splits: 57.5-77.5); 65 nodes 58.8-72.8, 58.2-71.2, 59.2-64.3,
+  // 59.2-61.6 (59.7-80.3).
+  auto rot_of = [&](int n_t) { return (int)((blockIdx.x * 5 + blockIdx.y * blockIdx.y * 3) % (uint32_t)n_t); };
   auto tile_row = [&](int lo, int n_t, int rot, int t) {
     const int x = t + rot;
     return (lo + (x >= n_t ? x - n_t : x)) * kKvTile;
