@@ -1,7 +1,6 @@
 // Host side of the respec_verify C ABI: plan creation (tiling choices and
 // workspace layout), argument validation and the launch sequence of one
 // verification step.  See include/respec_verify.h for the contract.
-#include <limits.h>
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
@@ -35,34 +34,16 @@ namespace {
 constexpr int kTargetWaves = 1024;  // attention: one wave per SIMD on a 256-CU MI355X
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
-int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
-// Register-path attention (tree_attn_kernel) of `rows` query rows per KV head:
-// rows are (node, head-in-group) pairs; a wave owns at most 32 of them (more
-// would not fit the registers next to a ring of tiles); above 4 waves' worth a
-// head's KV rows are read once per row block.
-struct RowGeom {
-  int nb, wr, wk, rows_per_wg, n_rowblk, threads;
-  size_t lds;
-};
-RowGeom row_geom(int es, int head_dim, int rows) {
-  RowGeom g;
-  g.nb = rows <= 16 ? 1 : 2;
-  const int rb = 16 * g.nb, rg = cdiv(rows, rb);
-  g.wr = rg < 4 ? rg : 4;
-  g.n_rowblk = cdiv(rg, g.wr);
-  g.wk = clampi(min(4 / g.wr, 128 / (g.wr * rb)), 1, 4);
-  g.rows_per_wg = g.wr * rb;
+// LDS of the register path's workgroup.
+size_t row_lds(int es, int head_dim, const RowGeom& g) {
   const int nwaves = g.wr * g.wk;
-  g.threads = 64 * nwaves;
   // per wave: one row-major, swizzled V tile (bf16) or one transposed, padded V tile (float32)
   const size_t vt = es == 2 ? (size_t)nwaves * kKvTile * head_dim * es
                             : (size_t)nwaves * head_dim * (kKvTile + kVtPad) * es;
   // wave merge: every wave's O lane-major (D/16 x NB blocks of 64 x 16 bytes) plus its m and l
   const size_t merge =
       g.wk > 1 ? (size_t)nwaves * ((size_t)(head_dim / 16) * g.nb * 64 * 16 + (size_t)2 * g.nb * 64 * 4) : 0;
-  g.lds = max(vt, merge);
-  return g;
+  return max(vt, merge);
 }
 bool aligned(const void* p, size_t n) { return ((uintptr_t)p % n) == 0; }
 
@@ -132,7 +113,7 @@ respec_status respec_verify_create(const respec_verify_shape* shape, respec_veri
     rows_per_wg = 32 * wr;
     slots = clampi(kCUs / (s.n_kv_heads * n_rowblk), 1, cdiv(t_cap, kKvTile));
   } else {
-    const RowGeom ge = row_geom(es, s.head_dim, rmax);
+    const RowGeom ge = row_geom(rmax);
     n_rowblk = ge.n_rowblk;
     rows_per_wg = ge.rows_per_wg;
     const int target = kTargetWaves / (ge.threads / 64) / (s.n_kv_heads * n_rowblk);
@@ -261,8 +242,9 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
 
   if (!plan->lds_ready.load(std::memory_order_acquire)) {
     for (int rows : {16, 32}) {  // (both row block counts; more row waves need no more)
-      const RowGeom ge = row_geom(plan->es, s.head_dim, rows);
-      if (set_tree_attn_lds_limit(s.dtype, s.head_dim, ge.nb, ge.lds) != hipSuccess) return RESPEC_ERR_HIP;
+      const RowGeom ge = row_geom(rows);
+      if (set_tree_attn_lds_limit(s.dtype, s.head_dim, ge.nb, row_lds(plan->es, s.head_dim, ge)) != hipSuccess)
+        return RESPEC_ERR_HIP;
     }
     if (plan->es == 2 && set_tree_attn_stream_lds_limit(s.head_dim) != hipSuccess) return RESPEC_ERR_HIP;
     plan->lds_ready.store(true, std::memory_order_release);
@@ -298,16 +280,12 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
   // One split per sequence: the attention kernel divides by its sums and writes x itself (96
   // sequences of 1-12 nodes over 100-1500 rows: the merge of 624 rows' single partials took 15 us).
   bool direct = false;
-  // More than one wave of rows: KV tiles shared through LDS.  Up to 32 rows the register
-  // path's four independent waves per workgroup are as fast or faster: 26 nodes over 2048
-  // rows of 32 heads 13.5 us against 15.7 us, 96 sequences of 1-12 nodes over 100-1500 rows
-  // 184 us against 196 us.  So they are for one sequence and two waves of rows while a CU has
-  // few tiles (its start-up is 3-4 us shorter, the second read of each tile comes from L2):
-  // 34 nodes of 32 heads over 1000 rows 14.0 against 17.0 us, over 4000 21.6 / 22.9, over 8000
-  // (32 tiles per CU) 31.9 / 30.3; 12 nodes on 8 heads of 4 over 4000 rows 11.4 / 15.0.
-  const long long tiles = (long long)cdiv((long long)a.max_kv_len_in_batch + a.max_nodes_in_batch, kKvTile) * s.n_kv_heads;
-  const bool few = a.batch == 1 && rows <= 64 && tiles <= 20ll * kCUs;
-  if (plan->es == 2 && rows > 32 && !few) {
+  const long long t_max = (long long)a.max_kv_len_in_batch + a.max_nodes_in_batch;
+  const int t_tiles = cdiv(t_max, kKvTile);
+  const AttnPath path = attn_path(plan->es, s.head_dim, s.n_kv_heads, a.batch, rows, t_tiles);
+  // splits (or pieces) whose partials the workspace holds
+  auto held = [&](int heads) { return plan->part_total / ((size_t)a.batch * heads * at.rows_per_wg); };
+  if (path == AttnPath::kStream) {
     const StreamGeom ge = stream_geom(plan, a.max_nodes_in_batch, a.max_kv_len_in_batch, a.batch);
     at.wr = ge.wr;
     at.n_rowblk = ge.n_rowblk;
@@ -320,40 +298,35 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
     ae = launch_tree_attn_stream(s.head_dim, ge.kg, dim3(ge.pieces, s.n_kv_heads * ge.n_rowblk, ge.slices), at, st,
                                  ev ? ev[0] : nullptr);
   } else {
-    const RowGeom ge = row_geom(plan->es, s.head_dim, rows);
+    const RowGeom ge = row_geom(rows);
     const int heads = s.n_kv_heads * ge.n_rowblk;
-    // splits (or pieces) whose partials the workspace holds
-    const int held = (int)min(plan->part_total / ((size_t)a.batch * heads * ge.rows_per_wg), (size_t)INT_MAX);
     const int wg_target = kTargetWaves / (ge.threads / 64);
-    const long long t_max = (long long)a.max_kv_len_in_batch + a.max_nodes_in_batch;
-    const int target = clampi(wg_target / (a.batch * heads), 1, min(held, cdiv(t_max, kKvTile)));
-    // (a split holds at least one tile per key-group wave: fewer, fuller splits for short caches)
-    at.chunk = max(cdiv(cdiv(t_max, target), kKvTile), ge.wk) * kKvTile;
-    at.nsplit = cdiv(t_max, at.chunk);
-    // Ragged batches: each head's KV tiles over every sequence are cut into
+    at.rows_per_wg = ge.rows_per_wg;
+    const Splits sp = kv_splits(wg_target, a.batch, heads, t_tiles, ge.wk, held(heads));
+    at.nsplit = sp.n;
+    at.chunk = sp.tiles * kKvTile;
+    // Long ragged batches: each head's KV tiles over every sequence are cut into
     // equal pieces, one workgroup each and one piece per CU, so that the longest
-    // sequence does not finish alone (per-sequence splits leave every other
-    // workgroup idle at the end; two pieces per CU measured slower on an
+    // sequence does not finish alone (two pieces per CU measured slower on an
     // 8-sequence ragged batch: 158 against 144 us).
-    const bool flat = a.batch > 1 && a.batch <= 64;
+    const bool flat = path == AttnPath::kFlat;
     if (flat) {
-      at.flat = at.nsplit = clampi(wg_target / heads, 1, min(held, 64));
+      at.flat = at.nsplit = clampi(wg_target / heads, 1, (int)min(held(heads), (size_t)64));
       at.chunk = 0;
     }
     at.n_rowblk = ge.n_rowblk;
-    merge_rows_per_blk = at.rows_per_wg = ge.rows_per_wg;
+    merge_rows_per_blk = ge.rows_per_wg;
     at.wr = ge.wr;
     at.wk = ge.wk;
     direct = !flat && at.nsplit == 1;
-    ae = launch_tree_attn(s.dtype, s.head_dim, ge.nb, dim3(at.nsplit, heads, flat ? 1 : a.batch), ge.threads, ge.lds,
-                          at, st, ev ? ev[0] : nullptr, ev && direct ? ev[1] : nullptr);
+    ae = launch_tree_attn(s.dtype, s.head_dim, ge.nb, dim3(at.nsplit, heads, flat ? 1 : a.batch), ge.threads,
+                          row_lds(plan->es, s.head_dim, ge),                          at, st, ev ? ev[0] : nullptr, ev && direct ? ev[1] : nullptr);
   }
   if (ae != hipSuccess) return RESPEC_ERR_HIP;
   // partials of a row: its sequence's splits, or of a batch that is cut into pieces about its share of them
-  const long long t_tiles = cdiv((long long)a.max_kv_len_in_batch + a.max_nodes_in_batch, kKvTile);
-  const int splits = at.pieces   ? (int)min((long long)cdiv(at.pieces, a.batch), max(1ll, t_tiles >> at.piece_shift))
-                     : at.flat ? cdiv(at.flat, a.batch)
-                               : at.nsplit;
+  const int splits = path == AttnPath::kStream ? min(cdiv(at.pieces, a.batch), max(1, t_tiles >> at.piece_shift))
+                     : path == AttnPath::kFlat ? cdiv(at.flat, a.batch)
+                                               : at.nsplit;
   if (!direct && launch_attn_merge(s.dtype, s.head_dim, at, merge_rows_per_blk, splits, st, ev ? ev[1] : nullptr) !=
                      hipSuccess)
     return RESPEC_ERR_HIP;

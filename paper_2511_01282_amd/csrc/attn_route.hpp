@@ -1,0 +1,97 @@
+// Which attention kernel a step takes, and how the KV rows are cut (host side, plain C++).
+#pragma once
+
+#include <limits.h>
+#include <stddef.h>
+
+namespace respec {
+
+constexpr int kCUs = 256;    // compute units of an MI355X
+constexpr int kKvTile = 32;  // KV rows per tile of the attention kernels
+
+enum class AttnPath {
+  kSplit,   // tree_attn_kernel: splits of each sequence (one split: no merge follows)
+  kFlat,    // tree_attn_kernel: equal pieces of the whole batch
+  kStream   // tree_attn_stream_kernel: equal pieces of the whole batch, as one stream per workgroup
+};
+
+// `rows` query rows per KV head of the largest tree, `tiles` KV tiles of the longest sequence (the
+// shorter ones are known to the device alone).  Figures: us per attention layer, merge included.
+inline AttnPath attn_path(int es, int head_dim, int n_kv_heads, int batch, int rows, long long tiles) {
+  const long long heads = (long long)batch * n_kv_heads;  // workgroups of one sequence and KV head each
+  const bool pieces_fit = batch > 1 && batch <= 64;       // (kFlat: a lane per sequence)
+  const long long splits = heads >= kCUs ? 1 : kCUs / heads, split_tiles = (tiles + splits - 1) / splits;
+  // A piece starts anew at every sequence it touches, 8 us each, and the partials are merged; a
+  // split that holds a whole sequence is not, but the longest sequence ends alone.  So the rows of a
+  // split decide.
+  if (es != 2) {
+    // 8 sequences, 8 heads of 64 columns, over 100-600 rows (splits of 150) splits 1.1 times as
+    // fast, over 300-2000 (500) the same, 24 sequences (2000) 0.7 times; with two row waves 4
+    // sequences over 300-2000 (250) 0.9 times.
+    return pieces_fit && split_tiles > (rows <= 32 ? 15 : 7) ? AttnPath::kFlat : AttnPath::kSplit;
+  }
+  if (rows <= 32) {
+    // 8 sequences of 32 nodes, 32 heads, splits / pieces: over 50-300 rows 14.8 / 33.9, 200-1000
+    // 23 / 34, 500-4000 62.8 / 62.8, 4000-16000 249 / 214.  With two pieces per sequence or more, as
+    // few KV heads leave, a piece seldom starts anew: 8 sequences of 8 heads of 4 over 1000-8000
+    // rows (splits of 2000) 34 / 31.  64 columns take half the time per row.
+    const bool many = n_kv_heads <= 16 && 2 * heads <= kCUs;
+    return pieces_fit && split_tiles * head_dim > (many ? 7600 : 12288) ? AttnPath::kFlat : AttnPath::kSplit;
+  }
+  if (batch == 1) {
+    // Two waves of rows while a CU has few tiles: the register path starts 3-4 us sooner, and the
+    // second read of each tile comes from L2.  34 nodes of 32 heads over 1000 rows 14.0 against 17.0
+    // us in a stream, over 4000 21.6 / 22.9, over 8000 (32 tiles per CU) 31.9 / 30.3; 12 nodes on 8
+    // heads of 4 over 4000 rows 11.4 / 15.0.
+    const long long cu_tiles = tiles * n_kv_heads;
+    if (rows <= 64 && cu_tiles <= 20ll * kCUs) return AttnPath::kSplit;
+    return AttnPath::kStream;
+  }
+  if (rows <= 128) {
+    // Few KV heads: 2-4 sequences of 17 nodes on 8 heads of 4 over up to 1000 rows 15-22 us in
+    // splits, 17-24 in a stream.
+    if (heads <= 32 && tiles <= 64) return AttnPath::kSplit;
+  }
+  return AttnPath::kStream;
+}
+
+inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
+inline int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
+
+// Register-path attention (tree_attn_kernel) of `rows` query rows per KV head:
+// rows are (node, head-in-group) pairs; a wave owns at most 32 of them (more
+// would not fit the registers next to a ring of tiles); above 4 waves' worth a
+// head's KV rows are read once per row block.
+struct RowGeom {
+  int nb, wr, wk, rows_per_wg, n_rowblk, threads;
+};
+inline RowGeom row_geom(int rows) {
+  RowGeom g;
+  g.nb = rows <= 16 ? 1 : 2;
+  const int rb = 16 * g.nb, rg = cdiv(rows, rb);
+  g.wr = rg < 4 ? rg : 4;
+  g.n_rowblk = cdiv(rg, g.wr);
+  g.rows_per_wg = g.wr * rb;
+  const int by_waves = 4 / g.wr, by_rows = 128 / g.rows_per_wg;
+  g.wk = clampi(by_waves < by_rows ? by_waves : by_rows, 1, 4);
+  g.threads = 64 * g.wr * g.wk;
+  return g;
+}
+
+// Splits of each sequence: as many as fill `wgs` workgroups over `heads` (KV head, row block) pairs
+// of `batch` sequences, of `least` tiles or more (one per key-group wave: fewer, fuller splits for
+// short caches), at most `held`.
+struct Splits {
+  int n, tiles;  // splits, tiles of each
+};
+inline Splits kv_splits(int wgs, int batch, int heads, long long tiles, int least, size_t held) {
+  const int most = held < (size_t)tiles ? (int)held : (int)tiles;
+  const int target = clampi((int)(wgs / ((long long)batch * heads)), 1, most);
+  Splits s;
+  s.tiles = cdiv(tiles, target);
+  if (s.tiles < least) s.tiles = least;
+  s.n = cdiv(tiles, s.tiles);
+  return s;
+}
+
+}  // namespace respec

@@ -298,17 +298,6 @@ __global__ __launch_bounds__(512) void tree_attn_stream_kernel(AttnArgs a) {
 
   auto seg_word = [&](int s, int w) { return __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(segs + s)[w]); };
 
-  // A segment's tiles are taken in rotated order, from a start that differs from
-  // workgroup to workgroup: heads and pieces lie at regular distances, and
-  // workgroups that all walk their tiles from the first one meet on the same
-  // memory channels where a head's rows take near a multiple of 2 MB plus or minus
-  // 32 KB.  The start is quadratic in the head: one that is linear (or none) moves
-  // the meeting to other cache capacities.  33 nodes of 32 heads over 15800 rows, us per
-  // attention layer at 50 capacities of 15872 to 16656 rows: by 5 x alone 55.4-69.3, by
-  // 5 x + 3 y 55.7-68.4, by 5 x + 17 y 55.0-61.5, this 56.0-58.4 (KV tiles in order, in a
-  // kernel of per-sequence splits: 57.5-77.5); 65 nodes 58.8-72.8, 58.2-71.2, 59.2-64.3,
-  // 59.2-61.6 (59.7-80.3).
-  auto rot_of = [&](int n_t) { return (int)((blockIdx.x * 5 + blockIdx.y * blockIdx.y * 3) % (uint32_t)n_t); };
   auto tile_row = [&](int lo, int n_t, int rot, int t) {
     const int x = t + rot;
     return (lo + (x >= n_t ? x - n_t : x)) * kKvTile;
@@ -339,7 +328,7 @@ __global__ __launch_bounds__(512) void tree_attn_stream_kernel(AttnArgs a) {
     pr.L = seg_word(s, 3);
     pr.lo = seg_word(s, 4);
     pr.n_t = seg_word(s, 5) - pr.lo;
-    pr.rot = rot_of(pr.n_t);
+    pr.rot = tile_rotation(pr.n_t);
     pr.t_rows = pr.L + n_nodes;
     pr.rows = n_nodes * a.group - row_wg;
     const int wr_live = min(a.wr, (pr.rows + 31) >> 5);
@@ -473,7 +462,7 @@ __global__ __launch_bounds__(512) void tree_attn_stream_kernel(AttnArgs a) {
     for (int db = 0; db < DB; ++db) o[db] = f32x16{};
 
     // passes of TP tiles, the first one of the remainder (so that the last is whole, or the only one)
-    const int rem = n_t % TP, rot = rot_of(n_t);
+    const int rem = n_t % TP, rot = tile_rotation(n_t);
     int c = rem ? rem : TP;
     for (int j = 0; j < n_t; j += c, c = TP) {
       begin_pass(c);

@@ -6,13 +6,13 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "attn_route.hpp"
+
 namespace respec {
 
-constexpr int kCUs = 256;        // compute units of an MI355X
 constexpr int kMaxNodes = 128;   // tree nodes per sequence (ancestor bitsets of 4 words)
 constexpr int kMaxDepth = 64;    // chain bits fit one 64-bit mask
 constexpr int kVtPad = 4;        // elements of padding per transposed-V row in LDS
-constexpr int kKvTile = 32;      // KV rows per wave step in the attention loop
 
 struct AttnArgs {
   const void* hidden;      // [M][Hd]

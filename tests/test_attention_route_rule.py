@@ -1,0 +1,75 @@
+"""The rule that picks the attention kernel, and the cut into splits (host code, on the CPU).
+
+Every GPU parity case names the path it is there for: this checks that it takes it, so that a later
+change of the rule cannot leave a kernel without its cases.
+"""
+import random
+
+import pytest
+
+import attn_paths
+import test_gpu_attention_routes as routes
+import test_gpu_split_merge as merge
+import test_gpu_stream_attention as stream
+
+
+@pytest.mark.parametrize("name", list(routes.CASES))
+def test_routes_cases(name):
+    hq, hkv, d, nodes, kv, want, dtype = (*routes.CASES[name], "bf16")[:7]
+    assert attn_paths.of(*routes.shape(hq, hkv, d), nodes, kv, dtype) == want
+
+
+@pytest.mark.parametrize("name", list(stream.CASES))
+def test_stream_cases(name):
+    hq, hkv, d, nodes, kv = stream.CASES[name][:5]
+    assert attn_paths.of(*routes.shape(hq, hkv, d), nodes, kv) == "stream"
+
+
+@pytest.mark.parametrize("name", list(merge.CASES))
+def test_merge_cases(name):
+    hq, hkv, d, nodes, kv, dtype, _, want = merge.CASES[name]
+    assert attn_paths.of(hq, hkv, d, nodes, kv, dtype) == want
+
+
+EDGES = [
+    # (bytes per element, D, KV heads, sequences, rows, tiles): path
+    ((2, 128, 32, 1, 64, 160), "split"), ((2, 128, 32, 1, 64, 161), "stream"),
+    ((2, 128, 32, 1, 96, 100), "stream"), ((2, 128, 32, 1, 97, 48), "stream"),
+    ((2, 128, 32, 1, 128, 321), "stream"), ((2, 64, 32, 1, 128, 100), "stream"),
+    ((2, 128, 32, 1, 129, 100), "stream"),
+    ((2, 128, 32, 8, 32, 96), "split"), ((2, 128, 32, 8, 32, 97), "flat"), ((2, 64, 32, 8, 32, 192), "split"),
+    ((2, 64, 32, 8, 32, 193), "flat"), ((2, 128, 32, 65, 32, 500), "split"), ((2, 128, 8, 8, 16, 236), "split"),
+    ((2, 128, 8, 8, 16, 240), "flat"), ((2, 128, 8, 17, 16, 96), "split"), ((2, 128, 8, 17, 16, 97), "flat"),
+    ((2, 64, 32, 24, 17, 13), "split"), ((2, 64, 32, 24, 16, 12), "split"),
+    ((2, 128, 8, 4, 128, 64), "split"), ((2, 128, 8, 4, 128, 65), "stream"), ((2, 128, 8, 4, 129, 64), "stream"),
+    ((2, 128, 32, 8, 128, 41), "stream"), ((2, 128, 8, 32, 64, 40), "stream"),
+    ((2, 64, 32, 12, 64, 65), "stream"), ((2, 64, 32, 12, 65, 64), "stream"),
+    ((2, 64, 32, 11, 64, 20), "stream"),
+    ((4, 64, 8, 8, 32, 60), "split"), ((4, 64, 8, 8, 32, 61), "flat"), ((4, 64, 8, 8, 33, 29), "flat"),
+    ((4, 64, 8, 65, 33, 500), "split"), ((4, 64, 8, 1, 500, 500), "split"),
+]
+
+
+@pytest.mark.parametrize("args,want", EDGES)
+def test_rule_edges(args, want):
+    assert attn_paths.path(*args) == want
+
+
+def test_splits_cover_every_tile():
+    """Any sizes: the splits cover the tiles, none is empty, and the workspace holds them."""
+    rng = random.Random(3)
+    for _ in range(20000):
+        wgs, batch, heads = rng.choice([256, 512]), rng.randint(1, 400), rng.randint(1, 300)
+        tiles, least = rng.randint(1, 5000), rng.randint(1, 4)
+        held = rng.choice([1, 2, 7, 64, 1 << 40])
+        n, per = attn_paths.splits(wgs, batch, heads, tiles, least, held)
+        assert 1 <= n <= held and per >= least
+        assert (n - 1) * per < tiles <= n * per
+
+
+def test_row_geometry():
+    """Any rows: the waves own them all, and a workgroup has four waves at most."""
+    for rows in range(1, 2000):
+        g = attn_paths.row_geometry(rows)
+        assert g["rows_per_wg"] == 16 * g["nb"] * g["wr"] and g["threads"] == 64 * g["wr"] * g["wk"] <= 256
+        assert (g["n_rowblk"] - 1) * g["rows_per_wg"] < rows <= g["n_rowblk"] * g["rows_per_wg"]

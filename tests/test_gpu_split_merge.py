@@ -21,24 +21,24 @@ from test_gpu_stream_attention import _rows_in_use, _tree
 pytestmark = pytest.mark.gpu
 
 CASES = {
-    # name: (Hq, Hkv, D, nodes per sequence, prefix lengths, dtype, plan's nodes)
-    "16-splits": (2, 2, 128, [5], [16 * 128 - 5], "bf16", 5),
-    "17-splits": (2, 2, 128, [5], [16 * 128 - 4], "bf16", 5),
-    "33-splits-d64": (4, 4, 64, [13], [33 * 128 - 13], "bf16", 61),
-    "17-splits-f32": (4, 4, 64, [16], [16 * 128 - 15], "f32", 16),
-    "33-splits-f32-d128": (4, 2, 128, [20], [1100], "f32", 61),
-    "pieces-of-a-batch": (4, 2, 64, [9, 3], [1500, 700], "bf16", 9),
-    "stream-16": (4, 1, 128, [40], [32 * 32 - 40], "bf16", 40),
-    "stream-17": (4, 1, 128, [40], [34 * 32 - 40], "bf16", 40),
-    "stream-64-larger-plan": (28, 4, 64, [17], [64 * 64 - 17], "bf16", 100),
-    "stream-of-a-batch": (4, 1, 128, [33, 40], [900, 2500], "bf16", 40),
+    # name: (Hq, Hkv, D, nodes per sequence, prefix lengths, dtype, plan's nodes, path)
+    "16-splits": (2, 2, 128, [5], [16 * 128 - 5], "bf16", 5, "split"),
+    "17-splits": (2, 2, 128, [5], [16 * 128 - 4], "bf16", 5, "split"),
+    "33-splits-d64": (4, 4, 64, [13], [33 * 128 - 13], "bf16", 61, "split"),
+    "17-splits-f32": (4, 4, 64, [16], [16 * 128 - 15], "f32", 16, "split"),
+    "33-splits-f32-d128": (4, 2, 128, [20], [1100], "f32", 61, "split"),
+    "pieces-of-a-batch": (4, 2, 64, [9, 3], [31000, 700], "f32", 9, "flat"),
+    "stream-16": (4, 1, 128, [40], [32 * 32 - 40], "bf16", 40, "stream"),
+    "stream-17": (4, 1, 128, [40], [34 * 32 - 40], "bf16", 40, "stream"),
+    "stream-64-larger-plan": (28, 4, 64, [17], [64 * 64 - 17], "bf16", 100, "stream"),
+    "stream-of-a-batch": (4, 1, 128, [33, 40], [900, 2500], "bf16", 40, "stream"),
 }
 
 
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("name", list(CASES))
 def test_split_merge(rt, name):  # noqa: F811
-    hq, hkv, d, nodes, kv, dtype, plan_nodes = CASES[name]
+    hq, hkv, d, nodes, kv, dtype, plan_nodes, _ = CASES[name]
     parents = [_tree(n, 2 + i % 3) for i, n in enumerate(nodes)]
     depth = max(8, max(_depth(p) for p in parents))
     shp = synth.Shape("edge", dtype, hq * d, hq, hkv, d, 520, len(nodes), max(nodes), depth, 8)
