@@ -246,7 +246,9 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
       if (set_tree_attn_lds_limit(s.dtype, s.head_dim, ge.nb, row_lds(plan->es, s.head_dim, ge)) != hipSuccess)
         return RESPEC_ERR_HIP;
     }
-    if (plan->es == 2 && set_tree_attn_stream_lds_limit(s.head_dim) != hipSuccess) return RESPEC_ERR_HIP;
+    if (plan->es == 2 && (set_tree_attn_stream_lds_limit(s.head_dim) != hipSuccess ||
+                          set_tree_attn_shared_lds_limit(s.head_dim) != hipSuccess))
+      return RESPEC_ERR_HIP;
     plan->lds_ready.store(true, std::memory_order_release);
   }
 
@@ -285,7 +287,17 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
   const AttnPath path = attn_path(plan->es, s.head_dim, s.n_kv_heads, a.batch, rows, t_tiles);
   // splits (or pieces) whose partials the workspace holds
   auto held = [&](int heads) { return plan->part_total / ((size_t)a.batch * heads * at.rows_per_wg); };
-  if (path == AttnPath::kStream) {
+  if (path == AttnPath::kShared) {
+    const int rg = cdiv(rows, 32);  // 1..4: two key groups
+    at.wr = rg;
+    at.n_rowblk = 1;
+    at.rows_per_wg = 32 * rg;
+    const Splits sp = kv_splits(kCUs, a.batch, s.n_kv_heads, t_tiles, 2, held(s.n_kv_heads));
+    at.nsplit = sp.n;
+    at.chunk = sp.tiles * kKvTile;
+    merge_rows_per_blk = rows;
+    ae = launch_tree_attn_shared(s.head_dim, dim3(at.nsplit, s.n_kv_heads, a.batch), at, st, ev ? ev[0] : nullptr);
+  } else if (path == AttnPath::kStream) {
     const StreamGeom ge = stream_geom(plan, a.max_nodes_in_batch, a.max_kv_len_in_batch, a.batch);
     at.wr = ge.wr;
     at.n_rowblk = ge.n_rowblk;

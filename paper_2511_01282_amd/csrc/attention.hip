@@ -18,9 +18,9 @@
 //     probabilities keep ~16 significant bits (bf16 P alone perturbs x enough
 //     to move logits by ~5e-4);
 //   - each wave keeps two KV tiles in flight while it processes a third.  (bf16
-//     with more than 32 query rows per KV head in the step runs in
-//     attn_stream.hip: there several waves need the same KV tile, and read it
-//     from LDS instead of loading it once each);
+//     with several waves of query rows per KV head: the waves need the same KV
+//     tiles, which a DMA ring brings into LDS instead, in the shared-tile variant
+//     below or in attn_stream.hip);
 //   - waves of a row group are merged in LDS; each workgroup writes an
 //     unnormalised partial (O, max, sum) per row;
 //   - a second, wide kernel (none where one split holds each sequence: Part::kWhole)
@@ -840,6 +840,334 @@ __global__ __launch_bounds__(256) void tree_attn_kernel(AttnArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Shared-tile variant (bf16; up to 4 waves of 32 query rows in each of two key
+// groups): splits of each sequence, where the streaming kernel (attn_stream.hip)
+// cuts the whole batch into pieces.  Its workgroups start and end by themselves,
+// two to a CU with 64-column heads, and its products are 16 rows high, so that a
+// wave with 16 live rows or fewer does half the work (attn_route.hpp: where it is
+// the faster one).  Every wave needs the same KV rows, so each KV tile is fetched
+// once per workgroup, straight into LDS by DMA (global_load_lds, 16 bytes per
+// lane), into a ring of S slots:
+//   - wave 0 requests the K half and wave 1 the V half of every tile;
+//   - a pass consumes TP = KG*TPG tiles (each of the KG key groups takes TPG
+//     of them, in tile order) while the next S-TP are in flight: a requesting
+//     wave waits until only its S-2*TP newest tiles are pending, then one
+//     barrier publishes the pass's tiles to every wave and, as every wave has
+//     finished the previous pass by then, frees that pass's slots for the
+//     tiles S ahead, requested right after.  Several tiles per pass (one
+//     barrier for all of them) let the waves of a SIMD drift apart within the
+//     pass instead of meeting at every tile;
+//   - the DMA requests are inline assembly (see dma_half_asm), so the K
+//     fragments (A operand of S^T = K Q^T) and the transposed V fragments are
+//     ordinary LDS reads that the compiler schedules; the barrier's own waits
+//     order them against the ring;
+//   - each wave owns 16*NB query rows of its own: no cross-wave merge.
+// K slot layout: 32 rows x D bf16, chunk c of row r at chunk position
+// c ^ kswz(r), so that a quarter-wave reading one chunk column of 16 rows hits
+// 64 distinct banks; V slots use the layout of the register path (vswz).
+template <int D>
+__device__ __forceinline__ int kswz(int r) {
+  return D == 128 ? (r & 15) : ((r >> 1) & 7);
+}
+
+// Request one half (K or V) of a 32-row tile into an LDS slot, 16 bytes per
+// lane (global_load_lds_dwordx4); rows at or past kv_hi are clamped to
+// kv_hi - 1 (masked, or weighted by zero, as above).  Issued as inline
+// assembly so that the compiler does not see an LDS write in flight: it then
+// schedules the ring's LDS reads freely (instead of waiting for every
+// outstanding request before each of them), and the kernel's own waits order
+// them.  The tile base is uniform (scalar registers), each lane adds a 32-bit
+// offset; M0 holds the LDS destination (saved and restored around the
+// request) and needs one wait state before the request.
+// Per-lane source offsets of a half-tile, one per DMA instruction (rows past
+// kv_hi clamped when the tile is not whole).  A whole tile's offsets do not
+// depend on the tile, so a requesting wave computes them once (DmaOffsets).
+template <int D, bool V>
+struct DmaLayout {
+  static constexpr int CPR = D * 2 / 16;  // 16-byte chunks per row
+  static constexpr int RPI = 64 / CPR;    // rows per DMA instruction (1 KB)
+  static constexpr int N = kKvTile / RPI;
+  __device__ __forceinline__ static uint32_t at(int q, int lane, int t0, int kv_hi, bool full) {
+    const int r = q * RPI + lane / CPR, pos = lane % CPR;
+    const int c = pos ^ (V ? vswz<D>(r) : kswz<D>(r));  // chunk that belongs at position pos
+    const int rr = full ? r : min(t0 + r, kv_hi - 1) - t0;  // rows past kv_hi: row kv_hi - 1 (t0 <= kv_hi - 1)
+    return (uint32_t)(rr * D * 2 + c * 16);
+  }
+};
+template <int D>
+struct DmaOffsets {
+  uint32_t off[DmaLayout<D, false>::N];
+  __device__ __forceinline__ void init(bool v_half, int lane) {  // v_half uniform
+#pragma unroll
+    for (int q = 0; q < DmaLayout<D, false>::N; ++q)
+      off[q] = v_half ? DmaLayout<D, true>::at(q, lane, 0, kKvTile, true) : DmaLayout<D, false>::at(q, lane, 0, kKvTile, true);
+  }
+};
+
+template <int D, bool V>
+__device__ __forceinline__ void dma_half_asm(uint32_t lds_dst, const char* base, int t0, int kv_hi, int lane,
+                                             const DmaOffsets<D>& pre) {
+  using O = DmaLayout<D, V>;
+  // the tile base and the LDS destination are uniform: made scalar explicitly for the asm operands
+  const uint64_t tb_u = reinterpret_cast<uint64_t>(base + (size_t)t0 * D * 2);
+  const uint64_t tb = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(tb_u >> 32)) << 32) |
+                      (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)tb_u);
+  lds_dst = __builtin_amdgcn_readfirstlane(lds_dst);
+  auto request = [&](int q, uint32_t off) {
+    uint32_t saved;
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %1\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %2, %3\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(saved)
+        : "s"(lds_dst + q * 1024), "v"(off), "s"(tb)
+        : "memory");
+  };
+  if (t0 + kKvTile <= kv_hi) {  // (uniform) a whole tile: the precomputed offsets
+#pragma unroll
+    for (int q = 0; q < O::N; ++q) request(q, pre.off[q]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < O::N; ++q) request(q, O::at(q, lane, t0, kv_hi, false));
+  }
+}
+
+template <int D>
+__global__ __launch_bounds__(512) void tree_attn_shared_kernel(AttnArgs a) {
+  constexpr int NB = 2, S = kSharedStages, KG = 2, TPG = 2;
+  constexpr int KCH = D * 2 / 64;
+  constexpr int DB = D / 16;
+  constexpr int RB = 16 * NB;
+  constexpr int kTile = kKvTile * D * 2;  // bytes of one K or V half-tile
+  constexpr int kStage = 2 * kTile;
+  constexpr int kLpt = kTile / 1024;      // DMA instructions per half-tile
+  constexpr int TP = KG * TPG;            // tiles per pass
+  static_assert(S > 2 * TP && (S - 2 * TP) * kLpt <= 63, "vmcnt holds at most 63 pending requests");
+
+  extern __shared__ __align__(16) unsigned char smem[];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)smem;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Roles: key group grp, row wave rw.  Waves w and w + 4 share a SIMD.  With two key groups
+  // the last row wave of each group holds the fewest live rows (65 rows: blocks 2, 2 and 1),
+  // so those two roles go to waves 0 and 1, whose SIMDs also carry waves 4 and 5: no SIMD then
+  // holds two full row waves of a three-wave group (65 rows: at most 3 blocks per SIMD, not 4).
+  int grp = wave, rw = a.wr - 1;
+  if (wave >= 2) {
+    const int j = wave - 2;
+    grp = j / (a.wr - 1);
+    rw = j - grp * (a.wr - 1);
+  }
+  grp = __builtin_amdgcn_readfirstlane(grp);
+  rw = __builtin_amdgcn_readfirstlane(rw);
+  const int lr = lane & 15, lg = lane >> 4;
+  const int b = blockIdx.z;
+  const int g = blockIdx.y / a.n_rowblk, rb = blockIdx.y % a.n_rowblk;
+  const int split = blockIdx.x;
+
+  const SeqRows sr = seq_rows(a, b);
+  const int node0 = sr.node0, n_nodes = sr.n_nodes, L = sr.L;
+  const int R = n_nodes * a.group;
+  const int row_wg = rb * a.rows_per_wg;
+  if (row_wg >= R) return;  // uniform over the workgroup
+
+  const size_t head_row0 = ((size_t)b * a.n_kv_heads + g) * (size_t)a.kv_cap;
+  const char* kbase = reinterpret_cast<const char*>(a.k_cache) + head_row0 * D * 2;
+  const char* vbase = reinterpret_cast<const char*>(a.v_cache) + head_row0 * D * 2;
+  const int t_rows = L + n_nodes;
+  const int kv_lo = split * a.chunk;
+  const int kv_hi = min(kv_lo + a.chunk, t_rows);
+  const int n_tiles = kv_lo < kv_hi ? (kv_hi - kv_lo + kKvTile - 1) / kKvTile : 0;
+  const int t_last = max(kv_hi - 1, 0);
+  const int rot = n_tiles > 0 ? tile_rotation(n_tiles) : 0;
+  auto tile_row = [&](int i) {  // (row of the i-th tile of the rotated order)
+    const int x = i + rot;
+    return i < n_tiles ? kv_lo + (x >= n_tiles ? x - n_tiles : x) * kKvTile : t_last;
+  };
+
+  int p_lo = a.parent[node0 + min(lane, n_nodes - 1)];
+  int p_hi = a.parent[node0 + min(lane + 64, n_nodes - 1)];
+  const int row_wave = row_wg + rw * RB;
+  u32x4 qf[NB][KCH];
+  int qnode[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int r = row_wave + 16 * nb + lr;
+    const bool live = r < R;
+    const int rc = live ? r : 0;
+    const int node = rc / a.group;
+    const int h = g * a.group + (rc - node * a.group);
+    qnode[nb] = live ? node : -1;
+    const char* src = reinterpret_cast<const char*>(a.hidden) +
+                      ((size_t)(node0 + node) * a.hidden_size + (size_t)h * D) * 2;
+#pragma unroll
+    for (int kc = 0; kc < KCH; ++kc) {
+      const u32x4 v = ld16(src + kc * 64 + lg * 16);
+      qf[nb][kc] = live ? v : u32x4{0, 0, 0, 0};
+    }
+  }
+
+  // Every wave has its parents and queries before the first requests are
+  // issued: the compiler's wait counts do not see the requests, so a value
+  // loaded before them and used after them would be waited for behind every
+  // request in flight (and the wait is shared by the waves that issue none).
+  asm volatile("" : "+v"(p_lo), "+v"(p_hi));
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int kc = 0; kc < KCH; ++kc) asm volatile("" : "+v"(qf[nb][kc]));
+  // the first S - TP tiles (kv_hi >= 1, so every clamped row is a valid cache row)
+  DmaOffsets<D> doff;  // wave 0: K halves, wave 1: V halves
+  if (wave < 2) doff.init(wave == 1, lane);
+  if (wave < 2) {
+#pragma unroll
+    for (int st = 0; st < S - TP; ++st) {
+      if (wave == 0)
+        dma_half_asm<D, false>(lds0 + st * kStage, kbase, tile_row(st), kv_hi, lane, doff);
+      else
+        dma_half_asm<D, true>(lds0 + st * kStage + kTile, vbase, tile_row(st), kv_hi, lane, doff);
+    }
+  }
+
+  float m_run[NB], l_run[NB];
+  f32x4 o[DB][NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    m_run[nb] = kNegInf;
+    l_run[nb] = 0.f;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  u32x4 anc[NB];
+  if (kv_hi > L)  // (uniform) only a split that reaches the tree's own rows needs the masks
+    ancestor_bits<NB>(qnode, p_lo, p_hi, n_nodes, anc);
+  else
+    for (int nb = 0; nb < NB; ++nb) anc[nb] = u32x4{0u, 0u, 0u, 0u};
+  // row blocks of this wave that hold a live row (blocks past the group's last row are skipped)
+  const int nbc = __builtin_amdgcn_readfirstlane(min(NB, max(0, (R - row_wave + 15) / 16)));
+
+  // Pass j consumes tiles TP*j .. TP*j+TP-1 (group q takes tiles TP*j + KG*r + q,
+  // r < TPG) from slots s0 .. s0+TP-1 (mod S); the slots of the previous pass's
+  // tiles are refilled with the tiles S ahead of them.
+  int s0 = 0;  // ring slot of tile TP*j
+  for (int j = 0; TP * j < n_tiles; ++j) {
+    // tiles TP*j .. TP*j+TP-1 have landed (a requesting wave waits for its own
+    // requests) and every wave's reads of the previous pass are done: one
+    // barrier covers both
+    if (wave < 2)
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"((S - 2 * TP) * kLpt) : "memory");
+    else
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (wave < 2) {
+#pragma unroll
+      for (int q = 0; q < TP; ++q) {
+        int sl = s0 - TP + q;
+        sl = sl < 0 ? sl + S : sl;
+        const int t_new = TP * j - TP + q + S;
+        if (wave == 0)
+          dma_half_asm<D, false>(lds0 + sl * kStage, kbase, tile_row(t_new), kv_hi, lane, doff);
+        else
+          dma_half_asm<D, true>(lds0 + sl * kStage + kTile, vbase, tile_row(t_new), kv_hi, lane, doff);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < TPG; ++r) {
+    const int t = TP * j + KG * r + grp;
+    if (t < n_tiles) {
+      int slot = s0 + KG * r + grp;
+      slot = slot >= S ? slot - S : slot;
+      const unsigned char* kt = smem + slot * kStage;
+      KTile<D> kf;
+      {
+        const int sw = kswz<D>(lr);  // kswz(16 + lr) == kswz(lr)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int kc = 0; kc < KCH; ++kc)
+            kf.k[kb][kc] = *reinterpret_cast<const u32x4*>(kt + (16 * kb + lr) * D * 2 + (((4 * kc + lg) ^ sw) << 4));
+      }
+      f32x4 s[2][NB];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          if (nb >= nbc) break;
+          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int kc = 0; kc < KCH; ++kc) acc = mma_k64(bf16_t{}, kf.k[kb][kc], qf[nb][kc], acc);
+          s[kb][nb] = acc;
+        }
+      u32x4 vf[DB];
+      read_vt_bf16<D>(kt + kTile, lane, vf);
+      u32x4 phi[NB], plo[NB];
+      softmax_p_bf16<D, NB>(s, tile_row(t), kv_hi, L, qnode, anc, a.scale_log2, m_run, l_run, o, lane, phi,
+                            plo, nbc);
+      pv_bf16<D, NB, DB>(vf, 0, phi, plo, o, nbc);
+    }
+    }
+    s0 += TP;
+    s0 = s0 >= S ? s0 - S : s0;
+  }
+  // the DMAs past the last tile must land before the workgroup's LDS is released
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    l_run[nb] += xchg<4>(l_run[nb]);
+    l_run[nb] += xchg<5>(l_run[nb]);
+  }
+  // Key group 1 hands its (max, sum, O) to group 0 through the ring's LDS,
+  // lane by lane (both hold the same rows in the same lanes):
+  //   M = max(m0, m1),  w_q = 2^(m_q - M),  l = w0 l0 + w1 l1,  O = w0 O0 + w1 O1.
+  constexpr int kX = DB * NB * 4 + 2 * NB;  // floats per lane
+  __syncthreads();  // every wave is done with the ring
+  float* xo = reinterpret_cast<float*>(smem) + (size_t)rw * kX * 64 + lane;
+  if (grp == 1) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xo[((nb * DB + db) * 4 + i) * 64] = o[db][nb][i];
+      xo[(DB * NB * 4 + 2 * nb) * 64] = m_run[nb];
+      xo[(DB * NB * 4 + 2 * nb + 1) * 64] = l_run[nb];
+    }
+  }
+  __syncthreads();
+  if (grp != 0) return;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const float m1 = xo[(DB * NB * 4 + 2 * nb) * 64], l1 = xo[(DB * NB * 4 + 2 * nb + 1) * 64];
+    const float M = fmaxf(m_run[nb], m1);
+    const float w0 = m_run[nb] == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m_run[nb] - M);
+    const float w1 = m1 == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m1 - M);
+    l_run[nb] = l_run[nb] * w0 + l1 * w1;
+    m_run[nb] = M;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[db][nb][i] = o[db][nb][i] * w0 + xo[((nb * DB + db) * 4 + i) * 64] * w1;
+  }
+  const int bgr = (b * a.n_kv_heads + g) * a.n_rowblk + rb;
+  const size_t pbase = ((size_t)bgr * a.nsplit + split) * a.rows_per_wg;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int rl = rw * RB + 16 * nb + lr;
+    if (row_wg + rl >= R) continue;  // rows past the group's last are never merged
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+      *reinterpret_cast<f32x4*>(a.part_o + (pbase + rl) * D + 16 * db + 4 * lg) = o[db][nb];
+    if (lg == 0) {
+      a.part_m[pbase + rl] = m_run[nb];
+      a.part_l[pbase + rl] = l_run[nb];
+    }
+  }
+}
+
 // Whose partials the merge reads: splits of each sequence, the register path's pieces, or the
 // streaming kernel's.  (One kernel each: as run-time branches, 26 nodes over 2048 rows 82.4 against
 // 81.9 us per step.)
@@ -1004,6 +1332,29 @@ hipError_t launch_tree_attn(int dtype, int head_dim, int nb, dim3 grid, int thre
   if (dtype == 1 && head_dim == 64) return launch_nb<bf16_t, 64>(nb, grid, threads, lds, a, s, ev_start, ev_stop);
   if (dtype == 0 && head_dim == 128) return launch_nb<float, 128>(nb, grid, threads, lds, a, s, ev_start, ev_stop);
   if (dtype == 0 && head_dim == 64) return launch_nb<float, 64>(nb, grid, threads, lds, a, s, ev_start, ev_stop);
+  return hipErrorInvalidValue;
+}
+
+template <int D>
+static hipError_t shared_ring(bool launch, dim3 grid, const AttnArgs& a, hipStream_t s, hipEvent_t ev_start) {
+  constexpr int kKg = 2, lds = kSharedStages * 2 * kKvTile * D * 2;
+  const auto kernel = tree_attn_shared_kernel<D>;
+  if (!launch)
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  return launch_k(kernel, grid, dim3(64 * a.wr * kKg), lds, s, ev_start, nullptr, a);
+}
+
+hipError_t launch_tree_attn_shared(int head_dim, dim3 grid, const AttnArgs& a, hipStream_t s, hipEvent_t ev_start) {
+  if (a.wr < 1 || a.wr > 4) return hipErrorInvalidValue;
+  if (head_dim == 128) return shared_ring<128>(true, grid, a, s, ev_start);
+  if (head_dim == 64) return shared_ring<64>(true, grid, a, s, ev_start);
+  return hipErrorInvalidValue;
+}
+
+hipError_t set_tree_attn_shared_lds_limit(int head_dim) {
+  const AttnArgs none{};
+  if (head_dim == 128) return shared_ring<128>(false, dim3(), none, nullptr, nullptr);
+  if (head_dim == 64) return shared_ring<64>(false, dim3(), none, nullptr, nullptr);
   return hipErrorInvalidValue;
 }
 

@@ -12,6 +12,7 @@ constexpr int kKvTile = 32;  // KV rows per tile of the attention kernels
 enum class AttnPath {
   kSplit,   // tree_attn_kernel: splits of each sequence (one split: no merge follows)
   kFlat,    // tree_attn_kernel: equal pieces of the whole batch
+  kShared,  // tree_attn_shared_kernel: splits of each sequence, KV tiles shared through LDS
   kStream   // tree_attn_stream_kernel: equal pieces of the whole batch, as one stream per workgroup
 };
 
@@ -31,6 +32,9 @@ inline AttnPath attn_path(int es, int head_dim, int n_kv_heads, int batch, int r
     return pieces_fit && split_tiles > (rows <= 32 ? 15 : 7) ? AttnPath::kFlat : AttnPath::kSplit;
   }
   if (rows <= 32) {
+    // 64-column heads fit two shared rings on a CU: many short sequences of 17-32 rows (64 of 32
+    // heads over 100-500 rows: shared 66, splits 79, pieces 132).
+    if (head_dim == 64 && rows > 16 && heads >= 3 * kCUs && 64 * tiles <= heads) return AttnPath::kShared;
     // 8 sequences of 32 nodes, 32 heads, splits / pieces: over 50-300 rows 14.8 / 33.9, 200-1000
     // 23 / 34, 500-4000 62.8 / 62.8, 4000-16000 249 / 214.  With two pieces per sequence or more, as
     // few KV heads leave, a piece seldom starts anew: 8 sequences of 8 heads of 4 over 1000-8000
@@ -45,12 +49,24 @@ inline AttnPath attn_path(int es, int head_dim, int n_kv_heads, int batch, int r
     // heads of 4 over 4000 rows 11.4 / 15.0.
     const long long cu_tiles = tiles * n_kv_heads;
     if (rows <= 64 && cu_tiles <= 20ll * kCUs) return AttnPath::kSplit;
+    // Four row waves in two groups: the stream's 32 x 32 products are short of work to hide in
+    // between (100 nodes of 32 heads, shared / stream: over 1000 rows 27.3 / 23.7, 2000 25.0 / 27.7,
+    // 4000 28.1 / 31.3, 8000 43.7 / 43.8, 32000 136 / 126; 128 nodes over 8000 49.0 / 52.6).
+    if (rows > 96 && rows <= 128 && head_dim == 128 && cu_tiles > 6ll * kCUs && cu_tiles <= 40ll * kCUs)
+      return AttnPath::kShared;
     return AttnPath::kStream;
   }
   if (rows <= 128) {
     // Few KV heads: 2-4 sequences of 17 nodes on 8 heads of 4 over up to 1000 rows 15-22 us in
     // splits, 17-24 in a stream.
     if (heads <= 32 && tiles <= 64) return AttnPath::kSplit;
+    // One short sequence per CU: 8 of 61 nodes, 32 heads, over 200-1000 rows 28.4 shared, 36.8 in a
+    // stream, 8 of 48 over 300-2000 49.6 and 44.5 (12 of 61 over 200-1000 54 and 46.8).
+    if (heads == kCUs && batch <= 8 && tiles <= 40) return AttnPath::kShared;
+    // Two shared rings on a CU hide each other's starts and ends: 32 of 48 nodes, 32 heads of 64
+    // columns, over 100-500 rows 41 shared and 69 in a stream, over 500-4000 (24 sequences) 96 and
+    // 104; 12 sequences over 500-4000 73 and 59.
+    if (head_dim == 64 && rows <= 64 && 2 * heads >= 3 * kCUs && 6 * tiles <= heads) return AttnPath::kShared;
   }
   return AttnPath::kStream;
 }

@@ -135,6 +135,12 @@ hipError_t set_tree_attn_lds_limit(int dtype, int head_dim, int nb, size_t lds);
 // device's lengths decide)
 hipError_t launch_attn_merge(int dtype, int head_dim, const AttnArgs& a, int rows_per_blk, int splits, hipStream_t s,
                              hipEvent_t ev_stop = nullptr);
+// bf16 only; a.wr (1..4) waves of 32 query rows in each of two key groups; KV tiles shared through
+// an LDS ring of kSharedStages K+V tiles; grid (splits, Hkv, batch)
+hipError_t launch_tree_attn_shared(int head_dim, dim3 grid, const AttnArgs& a, hipStream_t s,
+                                   hipEvent_t ev_start = nullptr);
+hipError_t set_tree_attn_shared_lds_limit(int head_dim);
+constexpr int kSharedStages = 10;  // ring slots (160 KB at head_dim 128)
 // bf16 streaming kernel: a.wr row waves (1..8) of 32 query rows in each of kg key groups
 // (4 for wr <= 2, 2 for wr <= 4, 1), grid (pieces, Hkv * n_rowblk, slices of kStreamSlice sequences)
 hipError_t launch_tree_attn_stream(int head_dim, int kg, dim3 grid, const AttnArgs& a, hipStream_t s,

@@ -6,7 +6,7 @@ import subprocess
 import tempfile
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2511_01282_amd", "csrc")
-NAMES = ("split", "flat", "stream")
+NAMES = ("split", "flat", "shared", "stream")
 
 _SOURCE = """
 #include "attn_route.hpp"

@@ -34,16 +34,16 @@ def test_merge_cases(name):
 EDGES = [
     # (bytes per element, D, KV heads, sequences, rows, tiles): path
     ((2, 128, 32, 1, 64, 160), "split"), ((2, 128, 32, 1, 64, 161), "stream"),
-    ((2, 128, 32, 1, 96, 100), "stream"), ((2, 128, 32, 1, 97, 48), "stream"),
-    ((2, 128, 32, 1, 128, 321), "stream"), ((2, 64, 32, 1, 128, 100), "stream"),
+    ((2, 128, 32, 1, 96, 100), "stream"), ((2, 128, 32, 1, 97, 100), "shared"), ((2, 128, 32, 1, 97, 48), "stream"),
+    ((2, 128, 32, 1, 128, 320), "shared"), ((2, 128, 32, 1, 128, 321), "stream"), ((2, 64, 32, 1, 128, 100), "stream"),
     ((2, 128, 32, 1, 129, 100), "stream"),
     ((2, 128, 32, 8, 32, 96), "split"), ((2, 128, 32, 8, 32, 97), "flat"), ((2, 64, 32, 8, 32, 192), "split"),
     ((2, 64, 32, 8, 32, 193), "flat"), ((2, 128, 32, 65, 32, 500), "split"), ((2, 128, 8, 8, 16, 236), "split"),
     ((2, 128, 8, 8, 16, 240), "flat"), ((2, 128, 8, 17, 16, 96), "split"), ((2, 128, 8, 17, 16, 97), "flat"),
-    ((2, 64, 32, 24, 17, 13), "split"), ((2, 64, 32, 24, 16, 12), "split"),
+    ((2, 64, 32, 24, 17, 12), "shared"), ((2, 64, 32, 24, 17, 13), "split"), ((2, 64, 32, 24, 16, 12), "split"),
     ((2, 128, 8, 4, 128, 64), "split"), ((2, 128, 8, 4, 128, 65), "stream"), ((2, 128, 8, 4, 129, 64), "stream"),
-    ((2, 128, 32, 8, 128, 41), "stream"), ((2, 128, 8, 32, 64, 40), "stream"),
-    ((2, 64, 32, 12, 64, 65), "stream"), ((2, 64, 32, 12, 65, 64), "stream"),
+    ((2, 128, 32, 8, 128, 40), "shared"), ((2, 128, 32, 8, 128, 41), "stream"), ((2, 128, 8, 32, 64, 40), "stream"),
+    ((2, 64, 32, 12, 64, 64), "shared"), ((2, 64, 32, 12, 64, 65), "stream"), ((2, 64, 32, 12, 65, 64), "stream"),
     ((2, 64, 32, 11, 64, 20), "stream"),
     ((4, 64, 8, 8, 32, 60), "split"), ((4, 64, 8, 8, 32, 61), "flat"), ((4, 64, 8, 8, 33, 29), "flat"),
     ((4, 64, 8, 65, 33, 500), "split"), ((4, 64, 8, 1, 500, 500), "split"),

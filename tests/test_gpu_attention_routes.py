@@ -4,6 +4,7 @@ Each case names its path (tests/test_attention_route_rule.py checks on the CPU t
   whole    the register path with one split per sequence, which writes its outputs without a merge;
   split    the register path with several;
   flat     the register path over pieces of the whole batch;
+  shared   KV tiles shared through LDS, splits of each sequence;
   stream   KV tiles shared through LDS, pieces of the whole batch (two key groups for batches of
            128-column heads and, up to 12 tiles per CU of 256, for 64-column ones, else four).
 
@@ -55,6 +56,15 @@ CASES = {
     "pieces-grouped": (16, 8, 128, [3, 16, 8, 1, 2, 7, 5, 9], [64, 7700, 0, 900, 31, 32, 33, 2000], "flat"),
     "pieces-f32": (8, 8, 64, [9, 30, 4, 1, 2, 3, 6, 5], [64, 2100, 0, 900, 31, 32, 33, 500], "flat", "f32"),
     "pieces-f32-two-waves": (16, 8, 64, [9, 30, 4, 1, 2, 3, 6, 5], [64, 1100, 0, 900, 31, 32, 33, 500], "flat", "f32"),
+    # shared tiles: one sequence of 97 to 128 rows, one short sequence per CU, many of 64-column heads
+    "shared-97-rows": (32, 32, 128, [97], [1500], "shared"),
+    "shared-128-rows-grouped": (32, 16, 128, [64], [3100], "shared"),
+    "shared-per-cu": (32, 32, 128, [33, 64, 1, 17, 40, 5, 12, 60], [300, 1100, 31, 32, 150, 0, 7, 200], "shared"),
+    "shared-per-cu-128-rows-d64": (64, 32, 64, [33, 64, 1, 17, 40, 5, 12, 60], [300, 600, 31, 32, 150, 0, 7, 200], "shared"),
+    "shared-many-d64": (8, 4, 64, [17] + [1 + k % 5 for k in range(269)], [150] + [(37 * k) % 120 for k in range(269)],
+                        "shared"),
+    "shared-many-32-rows": (8, 4, 64, [16] + [1 + k % 5 for k in range(199)], [300] + [(37 * k) % 200 for k in range(199)],
+                            "shared"),
     # streams
     "one-past-20-tiles": (64, 64, 64, [34], [80 * 32 - 33], "stream"),
     "one-long-d128": (32, 32, 128, [40], [5300], "stream"),
