@@ -42,6 +42,7 @@ inline AttnPath attn_path(int es, int head_dim, int n_kv_heads, int batch, int r
     const bool many = n_kv_heads <= 16 && 2 * heads <= kCUs;
     return pieces_fit && split_tiles * head_dim > (many ? 7600 : 12288) ? AttnPath::kFlat : AttnPath::kSplit;
   }
+  const bool half_idle = (rows - 1) % 32 < 16;  // the last wave of 32 rows
   if (batch == 1) {
     // Two waves of rows while a CU has few tiles: the register path starts 3-4 us sooner, and the
     // second read of each tile comes from L2.  34 nodes of 32 heads over 1000 rows 14.0 against 17.0
@@ -49,10 +50,10 @@ inline AttnPath attn_path(int es, int head_dim, int n_kv_heads, int batch, int r
     // heads of 4 over 4000 rows 11.4 / 15.0.
     const long long cu_tiles = tiles * n_kv_heads;
     if (rows <= 64 && cu_tiles <= 20ll * kCUs) return AttnPath::kSplit;
-    // Four row waves in two groups: the stream's 32 x 32 products are short of work to hide in
-    // between (100 nodes of 32 heads, shared / stream: over 1000 rows 27.3 / 23.7, 2000 25.0 / 27.7,
-    // 4000 28.1 / 31.3, 8000 43.7 / 43.8, 32000 136 / 126; 128 nodes over 8000 49.0 / 52.6).
-    if (rows > 96 && rows <= 128 && head_dim == 128 && cu_tiles > 6ll * kCUs && cu_tiles <= 40ll * kCUs)
+    // A last row wave with 16 live rows or fewer is half idle in the stream, whose products are 32
+    // rows high (32 heads, shared / stream: 65 nodes over 2100-3000 rows 0.92, 100 over 4000 28.1 / 31.3,
+    // over 8000 43.7 / 43.8; 96 over 3000 0.94, over 4000 1.12; 128 over 32000 1.15).
+    if (head_dim == 128 && rows <= 128 && half_idle && cu_tiles > 6ll * kCUs && cu_tiles <= 64ll * kCUs)
       return AttnPath::kShared;
     return AttnPath::kStream;
   }
@@ -60,6 +61,9 @@ inline AttnPath attn_path(int es, int head_dim, int n_kv_heads, int batch, int r
     // Few KV heads: 2-4 sequences of 17 nodes on 8 heads of 4 over up to 1000 rows 15-22 us in
     // splits, 17-24 in a stream.
     if (heads <= 32 && tiles <= 64) return AttnPath::kSplit;
+    // A few short ones whose last row wave is half idle (2 of 48 nodes, 32 heads, over 200-1000 rows
+    // 20.4 shared, 22.7 in a stream; 2 of 61 25.3 and 23.5, 48 nodes over 100-500 21.1 and 17.9).
+    if (batch <= 4 && n_kv_heads >= 16 && half_idle && tiles > 20 && tiles <= 40) return AttnPath::kShared;
     // One short sequence per CU: 8 of 61 nodes, 32 heads, over 200-1000 rows 28.4 shared, 36.8 in a
     // stream, 8 of 48 over 300-2000 49.6 and 44.5 (12 of 61 over 200-1000 54 and 46.8).
     if (heads == kCUs && batch <= 8 && tiles <= 40) return AttnPath::kShared;

@@ -34,9 +34,13 @@ def test_merge_cases(name):
 EDGES = [
     # (bytes per element, D, KV heads, sequences, rows, tiles): path
     ((2, 128, 32, 1, 64, 160), "split"), ((2, 128, 32, 1, 64, 161), "stream"),
+    ((2, 128, 32, 1, 48, 160), "split"), ((2, 128, 32, 1, 48, 161), "shared"), ((2, 128, 32, 1, 49, 161), "stream"),
     ((2, 128, 32, 1, 96, 100), "stream"), ((2, 128, 32, 1, 97, 100), "shared"), ((2, 128, 32, 1, 97, 48), "stream"),
-    ((2, 128, 32, 1, 128, 320), "shared"), ((2, 128, 32, 1, 128, 321), "stream"), ((2, 64, 32, 1, 128, 100), "stream"),
-    ((2, 128, 32, 1, 129, 100), "stream"),
+    ((2, 128, 32, 1, 112, 512), "shared"), ((2, 128, 32, 1, 112, 513), "stream"), ((2, 128, 32, 1, 113, 100), "stream"),
+    ((2, 64, 32, 1, 97, 100), "stream"), ((2, 128, 32, 1, 129, 100), "stream"),
+    ((2, 128, 16, 4, 33, 40), "shared"), ((2, 128, 16, 4, 33, 41), "stream"), ((2, 128, 16, 4, 33, 20), "stream"),
+    ((2, 128, 16, 5, 33, 40), "stream"), ((2, 64, 32, 2, 112, 21), "shared"), ((2, 64, 32, 2, 113, 21), "stream"),
+    ((2, 128, 32, 2, 129, 40), "stream"),
     ((2, 128, 32, 8, 32, 96), "split"), ((2, 128, 32, 8, 32, 97), "flat"), ((2, 64, 32, 8, 32, 192), "split"),
     ((2, 64, 32, 8, 32, 193), "flat"), ((2, 128, 32, 65, 32, 500), "split"), ((2, 128, 8, 8, 16, 236), "split"),
     ((2, 128, 8, 8, 16, 240), "flat"), ((2, 128, 8, 17, 16, 96), "split"), ((2, 128, 8, 17, 16, 97), "flat"),

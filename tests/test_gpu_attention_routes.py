@@ -56,9 +56,14 @@ CASES = {
     "pieces-grouped": (16, 8, 128, [3, 16, 8, 1, 2, 7, 5, 9], [64, 7700, 0, 900, 31, 32, 33, 2000], "flat"),
     "pieces-f32": (8, 8, 64, [9, 30, 4, 1, 2, 3, 6, 5], [64, 2100, 0, 900, 31, 32, 33, 500], "flat", "f32"),
     "pieces-f32-two-waves": (16, 8, 64, [9, 30, 4, 1, 2, 3, 6, 5], [64, 1100, 0, 900, 31, 32, 33, 500], "flat", "f32"),
-    # shared tiles: one sequence of 97 to 128 rows, one short sequence per CU, many of 64-column heads
+    # shared tiles: one sequence whose last row wave is at most half live, a few short sequences, one per
+    # CU, many of 64-column heads
     "shared-97-rows": (32, 32, 128, [97], [1500], "shared"),
-    "shared-128-rows-grouped": (32, 16, 128, [64], [3100], "shared"),
+    "shared-112-rows-grouped": (32, 16, 128, [56], [3100], "shared"),
+    "shared-65-rows": (32, 32, 128, [65], [1600], "shared"),
+    "shared-33-rows": (32, 32, 128, [33], [5120], "shared"),
+    "shared-a-few": (32, 32, 64, [41, 1, 33], [700, 0, 1100], "shared"),
+    "shared-a-few-grouped": (32, 16, 128, [9, 40, 2], [33, 700, 0], "shared"),
     "shared-per-cu": (32, 32, 128, [33, 64, 1, 17, 40, 5, 12, 60], [300, 1100, 31, 32, 150, 0, 7, 200], "shared"),
     "shared-per-cu-128-rows-d64": (64, 32, 64, [33, 64, 1, 17, 40, 5, 12, 60], [300, 600, 31, 32, 150, 0, 7, 200], "shared"),
     "shared-many-d64": (8, 4, 64, [17] + [1 + k % 5 for k in range(269)], [150] + [(37 * k) % 120 for k in range(269)],
@@ -67,10 +72,10 @@ CASES = {
                             "shared"),
     # streams
     "one-past-20-tiles": (64, 64, 64, [34], [80 * 32 - 33], "stream"),
-    "one-long-d128": (32, 32, 128, [40], [5300], "stream"),
+    "one-long-d128": (32, 32, 128, [50], [5300], "stream"),
     "batch-two-groups": (4, 2, 128, [17, 32, 1, 5], [70, 2100, 0, 31], "stream"),
     "batch-two-groups-d64": (4, 2, 64, [17, 1, 32, 5, 9], [2100, 0, 31, 32, 650], "stream"),
-    "batch-four-groups-d64": (32, 32, 64, [34, 5, 60, 1], [800, 0, 31, 90], "stream"),
+    "batch-four-groups-d64": (32, 32, 64, [34, 5, 60, 1, 2], [800, 0, 31, 90, 7], "stream"),
 }
 
 
