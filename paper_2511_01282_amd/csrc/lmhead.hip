@@ -640,6 +640,8 @@ struct TileCost {
 //     loop scales with the columns).  Larger tiles do more per byte that crosses
 //     the CU, smaller ones leave less of a last round, or of a last tile, empty.
 //     Measured / second best, us: 32000 rows by 142 tokens 72 / 77 (128 by 256),
+//     by 256 (whole step to the logits) 92.4 / 94.5 (128 by 256; 256 by 128 in the
+//     one-barrier kernel of 128 by 128 94.8), by 200 88.3 / 90.3,
 //     by 288 83 / 89, by 512 106 / 136, by 624 155 / 170, by 896 200 / 215;
 //     128256 rows by 128 210 / 218, by 384 390 / 410, by 510 455 / 560.
 LmTile lm_tile(int dtype, int M, int vocab) {
@@ -650,9 +652,9 @@ LmTile lm_tile(int dtype, int M, int vocab) {
     return M <= 16 ? LmTile::kPlain16 : M <= 32 ? LmTile::kPlain32 : M <= 48 ? LmTile::kPlain48 : LmTile::kPlain64;
   }
   static constexpr TileCost kCosts[] = {
-      {LmTile::kGemm128x128, 128, 128, 50}, {LmTile::kPair192x128, 192, 128, 62}, {LmTile::kPair128x256, 128, 256, 71},
-      {LmTile::kPair160x256, 160, 256, 78}, {LmTile::kPair192x256, 192, 256, 84}, {LmTile::kPair224x256, 224, 256, 91},
-      {LmTile::kPair256x256, 256, 256, 97}};
+      {LmTile::kGemm128x128, 128, 128, 50}, {LmTile::kPair192x128, 192, 128, 62}, {LmTile::kPair256x128, 256, 128, 68},
+      {LmTile::kPair128x256, 128, 256, 71}, {LmTile::kPair160x256, 160, 256, 78}, {LmTile::kPair192x256, 192, 256, 84},
+      {LmTile::kPair224x256, 224, 256, 91}, {LmTile::kPair256x256, 256, 256, 97}};
   LmTile best = LmTile::kPair256x256;
   long long least = -1;
   for (const TileCost& c : kCosts) {

@@ -291,6 +291,7 @@ hipError_t go(const LmArgs& a, hipStream_t s, hipEvent_t ev_stop) {
 hipError_t launch_lmhead_pair(LmTile tile, const LmArgs& a, hipStream_t s, hipEvent_t ev_stop) {
   switch (tile) {
     case LmTile::kPair192x128: return go<2, 3, 4, 3>(a, s, ev_stop);
+    case LmTile::kPair256x128: return go<2, 4, 4, 3>(a, s, ev_stop);
     case LmTile::kPair128x256: return go<4, 4, 3, 3>(a, s, ev_stop);
     case LmTile::kPair160x256: return go<4, 5, 3, 2>(a, s, ev_stop);
     case LmTile::kPair192x256: return go<4, 6, 3, 2>(a, s, ev_stop);

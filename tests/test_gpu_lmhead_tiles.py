@@ -1,7 +1,7 @@
 """GPU parity of the LM head's DMA-fed kernels (bf16), at the edges of their tiles.
 
 The token rows lie on both sides of every tile height the dispatch takes over these vocabularies
-(128 x 128, 192 x 128, then 128 to 256 by 256 in steps of 32), in one and several tiles; the
+(128, 192 and 256 by 128, then 128 to 256 by 256 in steps of 32), in one and several tiles; the
 vocabularies end inside a tile (one row, and odd counts that rule out 16-byte stores); up to 64 rows, the vocabulary
 leaves a last round of tiles of every height (64 to 256 rows), alone and after whole tiles; the hidden
 sizes give the shortest K loop (4 steps, as long as or shorter than the request rings hold) and
@@ -22,7 +22,7 @@ CASES = [
     # (token rows, hidden, vocab)
     (1, 256, 16449), (33, 512, 20001), (17, 256, 33001), (64, 768, 49153), (61, 256, 66003), (5, 512, 65600),
     (40, 256, 90004), (48, 256, 70000), (64, 256, 130001),
-    (65, 256, 32001), (128, 512, 520), (129, 256, 32001), (192, 768, 32004), (193, 256, 32001), (256, 1024, 32003),
+    (65, 256, 32001), (128, 512, 520), (129, 256, 32001), (192, 768, 32004), (193, 256, 32001), (224, 512, 20001), (256, 1024, 32003),
     (257, 256, 32004), (320, 512, 32001), (321, 256, 32002), (384, 768, 32001), (385, 256, 32001), (448, 512, 32004),
     (449, 256, 32257), (512, 768, 32001), (897, 512, 32001), (1025, 256, 1537),
 ]
