@@ -634,11 +634,19 @@ struct TileCost {
 //     (launch_lmhead).  Against the plain kernel, 4096 columns, us: 18000 rows by 26
 //     tokens 33 / 40, 24000 by 61 44 / 57, 32000 by 61 51 / 62, 128256 by 64 197 / 239.
 //     Up to 32 tokens and between 1.5 and 2 tiles per CU two plain workgroups per CU
-//     hold the whole vocabulary and are as fast: 32000 by 16 46 / 48.
+//     hold the whole vocabulary.  Steps to the logits, plain / 64 by 256, columns 2048,
+//     4096, 5120, 8192: 32000 words by 1 token 32 / 37, 54 / 57, 63 / 66, 115 / 120; by 17 38 / 42,
+//     62.4 / 62.8, 77 / 72, 128 / 127; by 26 40 / 44, 63.3 / 64.6, 82 / 74, 127 / 130; by 32
+//     42 / 45, 65.5 / 64.8, 84 / 76, 126 / 131.  At the lower end 64 by 256 is the better one for
+//     17-32 tokens (28000 by 26 39 / 38, 61 / 56, 80 / 69, 114 / 109) and level for fewer.
 //   - bf16, 65 rows and more: the tile with the fewest rounds of one tile per CU,
 //     weighted with the time of a round (measured at 4096 columns; every shape's
 //     loop scales with the columns).  Larger tiles do more per byte that crosses
 //     the CU, smaller ones leave less of a last round, or of a last tile, empty.
+//     A full round takes as long as its W rows from HBM, at least: 65-128 rows are
+//     bound by that with every shape, and the smaller tile's last round is shorter
+//     (65 rows over 70000 words 144 us per step with 128 by 128, 164 with 128 by 256,
+//     over 152064 254 and 268; over 128256, 1.96 rounds of 128 by 256, 214 and 212).
 //     Measured / second best, us: 32000 rows by 142 tokens 72 / 77 (128 by 256),
 //     by 256 (whole step to the logits) 92.4 / 94.5 (128 by 256; 256 by 128 in the
 //     one-barrier kernel of 128 by 128 94.8), by 200 88.3 / 90.3,
@@ -658,8 +666,11 @@ LmTile lm_tile(int dtype, int M, int vocab) {
   LmTile best = LmTile::kPair256x256;
   long long least = -1;
   for (const TileCost& c : kCosts) {
-    const long long tiles = (long long)((M + c.rows - 1) / c.rows) * ((vocab + c.vocab - 1) / c.vocab);
-    const long long t = (tiles + kCUs - 1) / kCUs * c.us;
+    const long long m_tiles = (M + c.rows - 1) / c.rows, tiles = m_tiles * ((vocab + c.vocab - 1) / c.vocab);
+    // (in ns; W arrives at 5.4 TB/s: 390 ns per vocabulary row of a tile on every CU, shared by its M tiles)
+    const long long us = 1000ll * c.us, stream = 390ll * c.vocab / m_tiles;
+    const long long full = us > stream ? us : stream, rest = tiles % kCUs * stream / kCUs;
+    const long long t = tiles / kCUs * full + (tiles % kCUs == 0 ? 0 : us > rest ? us : rest);
     if (least < 0 || t < least) {
       least = t;
       best = c.tile;

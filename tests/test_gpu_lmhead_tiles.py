@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
 CASES = [
     # (token rows, hidden, vocab)
     (1, 256, 16449), (33, 512, 20001), (17, 256, 33001), (64, 768, 49153), (61, 256, 66003), (5, 512, 65600),
-    (40, 256, 90004), (48, 256, 70000), (64, 256, 130001),
+    (40, 256, 90004), (9, 4096, 41001), (20, 8192, 33001), (48, 256, 70000), (64, 256, 130001),
     (65, 256, 32001), (128, 512, 520), (129, 256, 32001), (192, 768, 32004), (193, 256, 32001), (224, 512, 20001), (256, 1024, 32003),
     (257, 256, 32004), (320, 512, 32001), (321, 256, 32002), (384, 768, 32001), (385, 256, 32001), (448, 512, 32004),
     (449, 256, 32257), (512, 768, 32001), (897, 512, 32001), (1025, 256, 1537),
