@@ -719,7 +719,13 @@ hipError_t launch_lmhead(int dtype, LmTile tile, const LmArgs& a, hipStream_t s,
     // 152064 rows 222 / 211.
     LmArgs t = a;
     const int units = (a.vocab + 63) / 64, rounds = units / (4 * kCUs), left = units - rounds * 4 * kCUs;
-    const int h = (left + kCUs - 1) / kCUs;  // 0..4 units
+    int h = (left + kCUs - 1) / kCUs;  // 0..4 units
+    // Three units high, more than 208 tiles (any number, with rows of 16 KB) walk rows of 8 KB in
+    // each other's way: 1 row by 45000 words of 4096 columns 76.7 us per step, 72.7 with whole tiles
+    // (36000 words 60.7 / 63.4), of 8192 columns 163 / 143.  Rows of 7, 10, 12, 14, 24 and 32 KB do
+    // not (10 KB: 85.3 / 90.7).
+    const size_t row_bytes = (size_t)a.hidden_size * 2;
+    if (h == 3 && (row_bytes == 16384 || (row_bytes == 8192 && left > 3 * 208))) h = 4;
     t.full_tiles = rounds * kCUs;
     t.tail_rows = 64 * h;
     const int n = t.full_tiles + (h ? (left + h - 1) / h : 0);
