@@ -910,9 +910,7 @@ __device__ __forceinline__ void dma_half_asm(uint32_t lds_dst, const char* base,
                                              const DmaOffsets<D>& pre) {
   using O = DmaLayout<D, V>;
   // the tile base and the LDS destination are uniform: made scalar explicitly for the asm operands
-  const uint64_t tb_u = reinterpret_cast<uint64_t>(base + (size_t)t0 * D * 2);
-  const uint64_t tb = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(tb_u >> 32)) << 32) |
-                      (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)tb_u);
+  const uint64_t tb = uniform_u64(reinterpret_cast<uint64_t>(base + (size_t)t0 * D * 2));
   lds_dst = __builtin_amdgcn_readfirstlane(lds_dst);
   auto request = [&](int q, uint32_t off) {
     uint32_t saved;

@@ -94,11 +94,6 @@ __device__ __forceinline__ float max2(float a, float b) {
   return __builtin_amdgcn_fmed3f(a, b, __builtin_huge_valf());
 }
 
-__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
-  return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
-         (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
-}
-
 // N DMA requests of 1 KB (global_load_lds_dwordx4, 16 bytes per lane): request i
 // moves 16 bytes per lane from base + off[i] + 1024 i into LDS at dst + 1024 i
 // (the instruction's offset counts on both sides; dst and base uniform).
@@ -106,7 +101,7 @@ template <int N>
 __device__ __forceinline__ void dma16(uint32_t dst, uint64_t base, const uint32_t* off) {
   uint32_t saved;
   dst = __builtin_amdgcn_readfirstlane(dst);
-  base = uniform64(base);
+  base = uniform_u64(base);
   if constexpr (N == 2) {
     asm volatile(
         "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
@@ -116,7 +111,8 @@ __device__ __forceinline__ void dma16(uint32_t dst, uint64_t base, const uint32_
         : "=&s"(saved)
         : "s"(dst), "v"(off[0]), "v"(off[1]), "s"(base)
         : "memory");
-  } else if constexpr (N == 4) {
+  } else {
+    static_assert(N == 4, "requests per producer and slot");
     asm volatile(
         "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
         "global_load_lds_dwordx4 %2, %6\n\t"
@@ -127,16 +123,12 @@ __device__ __forceinline__ void dma16(uint32_t dst, uint64_t base, const uint32_
         : "=&s"(saved)
         : "s"(dst), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base)
         : "memory");
-  } else {
-    static_assert(N == 8, "requests per producer and slot");
-    dma16<4>(dst, base, off);
-    dma16<4>(dst + 4096, base + 4096, off + 4);
   }
 }
 __device__ __forceinline__ void dma4(uint32_t dst, uint64_t base, uint32_t off) {  // 4 bytes per lane
   uint32_t saved;
   dst = __builtin_amdgcn_readfirstlane(dst);
-  base = uniform64(base);
+  base = uniform_u64(base);
   asm volatile(
       "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
       "global_load_lds_dword %2, %3\n\t"
@@ -165,9 +157,10 @@ __device__ __forceinline__ u32x4 ancestor_set(const int32_t* par, int node, int 
   return anc;
 }
 
-template <int D, int S, int KG, int TPG, int PW>
+template <int D, int S, int KG, int TPG>
 struct StreamShape {
   static constexpr int TP = KG * TPG;                    // slots per pass
+  static constexpr int PW = 4;                           // producer waves
   static constexpr int kHalf = kKvTile * D * 2;          // bytes of a K or V half slot
   static constexpr int kSlot = 2 * kHalf;
   static constexpr int NR = kHalf / 1024 / (PW / 2);     // DMA requests of a producer per slot
@@ -185,11 +178,12 @@ struct StreamShape {
   static_assert(kLds <= 163840, "LDS of a CU");
 };
 
-template <int D, int S, int KG, int TPG, int PW>
+template <int D, int S, int KG, int TPG>
 __global__ __launch_bounds__(512) void tree_attn_stream_kernel(AttnArgs a) {
-  using G = StreamShape<D, S, KG, TPG, PW>;
+  using G = StreamShape<D, S, KG, TPG>;
   constexpr int NR = G::NR;
   constexpr int TP = G::TP;
+  constexpr int PW = G::PW;
   constexpr int KS = D / 16;   // 16-element slices of a head row
   constexpr int DB = D / 32;   // 32-column blocks of O
   constexpr int DH = DB / 2;   // ... per hand-over round
@@ -644,27 +638,22 @@ __global__ __launch_bounds__(512) void tree_attn_stream_kernel(AttnArgs a) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-template <int D, int S, int KG, int TPG, int PW>
+template <int D, int S, int KG, int TPG>
 hipError_t go(bool launch, dim3 grid, int threads, const AttnArgs& a, hipStream_t s, hipEvent_t ev_start) {
-  using G = StreamShape<D, S, KG, TPG, PW>;
+  using G = StreamShape<D, S, KG, TPG>;
   if (!launch)
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&tree_attn_stream_kernel<D, S, KG, TPG, PW>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&tree_attn_stream_kernel<D, S, KG, TPG>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, G::kLds);
-  if (a.wr < 1 || a.wr > G::kMaxWr || threads != 64 * a.wr * KG || threads < 64 * PW) return hipErrorInvalidValue;
-  return launch_k(tree_attn_stream_kernel<D, S, KG, TPG, PW>, grid, dim3(threads), G::kLds, s, ev_start, nullptr, a);
+  if (a.wr < 1 || a.wr > G::kMaxWr || threads != 64 * a.wr * KG || threads < 64 * G::PW) return hipErrorInvalidValue;
+  return launch_k(tree_attn_stream_kernel<D, S, KG, TPG>, grid, dim3(threads), G::kLds, s, ev_start, nullptr, a);
 }
 
 template <int D>
 hipError_t go_kg(int kg, bool launch, dim3 grid, int threads, const AttnArgs& a, hipStream_t s, hipEvent_t ev_start) {
   switch (kg) {
-    case 1: return go<D, 9, 1, 4, 4>(launch, grid, threads, a, s, ev_start);
-    case 2:
-      if (!launch || threads < 256) {
-        const hipError_t e = go<D, 9, 2, 2, 2>(launch, grid, threads, a, s, ev_start);
-        if (launch || e != hipSuccess) return e;
-      }
-      return go<D, 9, 2, 2, 4>(launch, grid, threads, a, s, ev_start);
-    case 4: return go<D, 9, 4, 1, 4>(launch, grid, threads, a, s, ev_start);
+    case 1: return go<D, 9, 1, 4>(launch, grid, threads, a, s, ev_start);
+    case 2: return go<D, 9, 2, 2>(launch, grid, threads, a, s, ev_start);
+    case 4: return go<D, 9, 4, 1>(launch, grid, threads, a, s, ev_start);
     default: return hipErrorInvalidValue;
   }
 }

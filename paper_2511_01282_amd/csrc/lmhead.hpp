@@ -24,11 +24,6 @@ __device__ __forceinline__ void gm_dma(uint32_t lds_dst, uint64_t base, uint32_t
       : "memory");
 }
 
-__device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
-  return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
-         (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
-}
-
 // Statistics {max, sum, entropy sum, argmax} of one token row's logits z of the 64-row statistics tile at vh
 // (entries at or past V are not logits), by one thread.
 __device__ __forceinline__ void tile_row_stats(const f32x4* z4, int vh, int vocab, float* dst) {
