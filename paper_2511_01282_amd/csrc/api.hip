@@ -25,8 +25,8 @@ struct respec_verify_plan {
   size_t off_span;        // first and last piece of each sequence (dead before the LM head's statistics)
   size_t part_total;      // rows of attention partials that the workspace holds
   size_t n_cnt_seq, total;
-  // the attention kernel's LDS limit is raised on the first step (plan creation stays GPU-free)
-  mutable std::atomic<bool> lds_ready{false};
+  // kernel families (LdsUser bits) whose LDS limits are raised: on their first step (plan creation stays GPU-free)
+  mutable std::atomic<uint32_t> lds_ready{0};
 };
 
 namespace {
@@ -190,6 +190,32 @@ StreamGeom stream_geom(const respec_verify_plan* p, int n, int max_kv, int batch
   return g;
 }
 
+constexpr int kMaxDevices = 64;
+
+// Raise the LDS limits of the attention kernels that a path of this dtype and head size may launch, on
+// the current device, once (calls into the runtime that also load the kernels: the first step that
+// takes the path pays them, not every plan's).
+enum LdsUser { kLdsRegister, kLdsShared, kLdsStream };
+bool raise_lds_limits(LdsUser user, int dtype, int es, int head_dim) {
+  static std::atomic<uint64_t> done[3][2][2];  // [user][dtype][head size], a bit per device
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return false;
+  std::atomic<uint64_t>& d = done[user][dtype == RESPEC_BF16][head_dim == 128];
+  const uint64_t bit = dev < kMaxDevices ? 1ull << dev : 0;  // (past the last: every plan raises them)
+  if (d.load(std::memory_order_acquire) & bit) return true;
+  if (user == kLdsRegister) {
+    for (int rows : {16, 32}) {  // (both row block counts; more row waves need no more)
+      const RowGeom ge = row_geom(rows);
+      if (set_tree_attn_lds_limit(dtype, head_dim, ge.nb, row_lds(es, head_dim, ge)) != hipSuccess) return false;
+    }
+  } else if ((user == kLdsShared ? set_tree_attn_shared_lds_limit(head_dim) : set_tree_attn_stream_lds_limit(head_dim)) !=
+             hipSuccess) {
+    return false;
+  }
+  d.fetch_or(bit, std::memory_order_release);
+  return true;
+}
+
 // One step on workspace `ws` (the plan's layout) with the sequences' completion
 // counters at `cnt` (zero between steps).
 respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args* args, char* ws, int32_t* cnt,
@@ -239,19 +265,6 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
     return RESPEC_ERR_SHAPE;
   const bool rank = vocab_pass && a.tok_rank != nullptr;
 
-
-  if (!plan->lds_ready.load(std::memory_order_acquire)) {
-    for (int rows : {16, 32}) {  // (both row block counts; more row waves need no more)
-      const RowGeom ge = row_geom(rows);
-      if (set_tree_attn_lds_limit(s.dtype, s.head_dim, ge.nb, row_lds(plan->es, s.head_dim, ge)) != hipSuccess)
-        return RESPEC_ERR_HIP;
-    }
-    if (plan->es == 2 && (set_tree_attn_stream_lds_limit(s.head_dim) != hipSuccess ||
-                          set_tree_attn_shared_lds_limit(s.head_dim) != hipSuccess))
-      return RESPEC_ERR_HIP;
-    plan->lds_ready.store(true, std::memory_order_release);
-  }
-
   // ---- tree-masked attention + residual ----
   AttnArgs at;
   at.hidden = a.hidden;
@@ -285,6 +298,11 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
   const long long t_max = (long long)a.max_kv_len_in_batch + a.max_nodes_in_batch;
   const int t_tiles = cdiv(t_max, kKvTile);
   const AttnPath path = attn_path(plan->es, s.head_dim, s.n_kv_heads, a.batch, rows, t_tiles);
+  const LdsUser user = path == AttnPath::kShared ? kLdsShared : path == AttnPath::kStream ? kLdsStream : kLdsRegister;
+  if (!(plan->lds_ready.load(std::memory_order_acquire) & (1u << user))) {
+    if (!raise_lds_limits(user, s.dtype, plan->es, s.head_dim)) return RESPEC_ERR_HIP;
+    plan->lds_ready.fetch_or(1u << user, std::memory_order_release);
+  }
   // splits (or pieces) whose partials the workspace holds
   auto held = [&](int heads) { return plan->part_total / ((size_t)a.batch * heads * at.rows_per_wg); };
   if (path == AttnPath::kShared) {
@@ -332,7 +350,8 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
     at.wk = ge.wk;
     direct = !flat && at.nsplit == 1;
     ae = launch_tree_attn(s.dtype, s.head_dim, ge.nb, dim3(at.nsplit, heads, flat ? 1 : a.batch), ge.threads,
-                          row_lds(plan->es, s.head_dim, ge),                          at, st, ev ? ev[0] : nullptr, ev && direct ? ev[1] : nullptr);
+                          row_lds(plan->es, s.head_dim, ge), at, st, ev ? ev[0] : nullptr,
+                          ev && direct ? ev[1] : nullptr);
   }
   if (ae != hipSuccess) return RESPEC_ERR_HIP;
   // partials of a row: its sequence's splits, or of a batch that is cut into pieces about its share of them
@@ -464,7 +483,6 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
 constexpr size_t kScratchBytes = (size_t)RESPEC_NOALLOC_SCRATCH_BYTES;
 constexpr size_t kScratchCounterBytes = (size_t)RESPEC_NOALLOC_MAX_BATCH * 4;
 static_assert(kScratchCounterBytes % 256 == 0, "the workspace after the counters stays 256-byte aligned");
-constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
