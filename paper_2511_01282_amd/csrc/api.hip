@@ -5,6 +5,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <new>
@@ -22,7 +23,7 @@ struct respec_verify_plan {
   int ko, n_vtiles;
   // workspace layout (bytes)
   size_t off_po, off_pm, off_pl, off_x, off_part, off_flag, off_cnt, off_stoch, off_rank;
-  size_t off_span;        // first and last piece of each sequence (dead before the LM head's statistics)
+  size_t off_span;        // first and last piece of each sequence (dead before the LM head's statistics and the flags)
   size_t part_total;      // rows of attention partials that the workspace holds
   size_t n_cnt_seq, total;
   // kernel families (LdsUser bits) whose LDS limits are raised: on their first step (plan creation stays GPU-free)
@@ -43,7 +44,7 @@ size_t row_lds(int es, int head_dim, const RowGeom& g) {
   // wave merge: every wave's O lane-major (D/16 x NB blocks of 64 x 16 bytes) plus its m and l
   const size_t merge =
       g.wk > 1 ? (size_t)nwaves * ((size_t)(head_dim / 16) * g.nb * 64 * 16 + (size_t)2 * g.nb * 64 * 4) : 0;
-  return max(vt, merge);
+  return std::max(vt, merge);
 }
 bool aligned(const void* p, size_t n) { return ((uintptr_t)p % n) == 0; }
 
@@ -133,10 +134,13 @@ respec_status respec_verify_create(const respec_verify_shape* shape, respec_veri
   p->off_x = off; off = align256(off + mcap * s.hidden * es);
   p->part_total = prow;
   const size_t part_bytes = mcap * p->n_vtiles * kTileWords * 4;
-  const size_t span_bytes = (size_t)s.max_batch * s.n_kv_heads * cdiv(rmax, 256) * 8;
-  p->off_span = off;  // shared with the LM head's statistics, which are written after the split merge
-  p->off_part = off; off = align256(off + (part_bytes > span_bytes ? part_bytes : span_bytes));
+  p->off_part = off; off = align256(off + part_bytes);
   p->off_flag = off; off = align256(off + mcap * 4);
+  // the streaming kernel's spans lie over the LM head's statistics and the flags, which are written
+  // after the split merge has read them (one sequence has none)
+  const bool spans = es == 2 && rmax > 32 && s.max_batch > 1;
+  p->off_span = p->off_part;
+  if (spans) off = std::max(off, align256(p->off_span + (size_t)s.max_batch * s.n_kv_heads * cdiv(rmax, 256) * 8));
   p->n_cnt_seq = s.max_batch;
   p->off_cnt = off; off = align256(off + p->n_cnt_seq * 4);
   p->off_stoch = off; off = align256(off + 2 * mcap * 4);  // stochastic walk: next child, draw
@@ -186,7 +190,7 @@ StreamGeom stream_geom(const respec_verify_plan* p, int n, int max_kv, int batch
   const int heads = p->s.n_kv_heads * g.n_rowblk;
   // one workgroup per CU, within the partial rows that the workspace holds
   const long long blocks = (long long)(p->part_total / ((size_t)heads * g.part_rows));
-  g.pieces = (int)max(1ll, min((long long)(kCUs / heads), (blocks - batch) / g.slices + 1));
+  g.pieces = (int)std::max(1ll, std::min((long long)(kCUs / heads), (blocks - batch) / g.slices + 1));
   return g;
 }
 
@@ -341,7 +345,7 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
     // 8-sequence ragged batch: 158 against 144 us).
     const bool flat = path == AttnPath::kFlat;
     if (flat) {
-      at.flat = at.nsplit = clampi(wg_target / heads, 1, (int)min(held(heads), (size_t)64));
+      at.flat = at.nsplit = clampi(wg_target / heads, 1, (int)std::min(held(heads), (size_t)64));
       at.chunk = 0;
     }
     at.n_rowblk = ge.n_rowblk;

@@ -77,3 +77,25 @@ def test_row_geometry():
         g = attn_paths.row_geometry(rows)
         assert g["rows_per_wg"] == 16 * g["nb"] * g["wr"] and g["threads"] == 64 * g["wr"] * g["wk"] <= 256
         assert (g["n_rowblk"] - 1) * g["rows_per_wg"] < rows <= g["n_rowblk"] * g["rows_per_wg"]
+
+
+@pytest.mark.parametrize("dtype,batch,nodes", [(0, 64, 1), (1, 64, 1), (1, 1, 61)])
+def test_workspace_holds_no_spans_where_no_stream_has_them(dtype, batch, nodes):
+    """float32, at most 32 rows per KV head, one sequence: the vocabulary's statistics alone grow with it."""
+    import ctypes
+    from paper_2511_01282_amd import binding
+
+    def size(vocab):
+        h = ctypes.c_void_p()
+        s = binding.Shape(64 * 128, 64, 64, 128, vocab, dtype, batch, nodes, 8, 4000, 1)
+        assert binding.lib().respec_verify_create(ctypes.byref(s), ctypes.byref(h)) == binding.OK
+        n = binding.lib().respec_verify_workspace_bytes(h)
+        binding.lib().respec_verify_destroy(h)
+        return n
+
+    def aligned(n):
+        return -(-n // 256) * 256
+
+    rows = batch * nodes
+    for tiles in range(1, 40):
+        assert size(64 * tiles + 64) - size(64 * tiles) == aligned(16 * rows * (tiles + 1)) - aligned(16 * rows * tiles)
