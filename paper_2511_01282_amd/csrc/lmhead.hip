@@ -729,7 +729,10 @@ hipError_t launch_lmhead(int dtype, LmTile tile, const LmArgs& a, hipStream_t s,
     t.full_tiles = rounds * kCUs;
     t.tail_rows = 64 * h;
     const int n = t.full_tiles + (h ? (left + h - 1) / h : 0);
-    return launch_k(lmhead_gemm_kernel<64, 256, true>, dim3((n + 7) / 8 * 8), blk, 0, s, nullptr, ev_stop, t);
+    const dim3 grid((n + 7) / 8 * 8);
+    // (whole tiles throughout: without the low tiles' tests in the loop)
+    if (h == 0 || h == 4) return launch_k(lmhead_gemm_kernel<64, 256, false>, grid, blk, 0, s, nullptr, ev_stop, a);
+    return launch_k(lmhead_gemm_kernel<64, 256, true>, grid, blk, 0, s, nullptr, ev_stop, t);
   }
   if (tile == LmTile::kGemm128x128) {
     const int n = (a.vocab + 127) / 128;
