@@ -69,18 +69,20 @@ def stage_bytes(w, M, es):
     return dict(attn=attn, lm=lm, vocab=vocab, attn_flops=attn_flops, lm_flops=lm_flops)
 
 
-STAGE_SOURCES = {"attention": ("attention.hip", "AttnArgs"), "lm_head": ("lmhead.hip", "LmArgs"),
-                 "vocab_pass": ("vocab.hip", "VocabArgs")}
+STAGE_SOURCES = {
+    "attention": (("attention.hip", "attn_stream.hip", "attention.hpp", "attn_route.hpp"), "AttnArgs"),
+    "lm_head": (("lmhead.hip", "lmhead_pair.hip", "lmhead.hpp"), "LmArgs"),
+    "vocab_pass": (("vocab.hip",), "VocabArgs")}
 
 
 def stage_source_hash(stage):
-    """Hash of what a stage's kernels are compiled from: its .hip file, common.hpp and its
+    """Hash of what a stage's kernels are compiled from: its sources, common.hpp and its
     argument struct in kernels.hpp (the other declarations there do not change it)."""
     import hashlib
-    src, struct = STAGE_SOURCES[stage]
+    sources, struct = STAGE_SOURCES[stage]
     csrc = os.path.join(ROOT, "paper_2511_01282_amd", "csrc")
     h = hashlib.sha256()
-    for f in (src, "common.hpp"):
+    for f in sources + ("common.hpp",):
         with open(os.path.join(csrc, f), "rb") as fh:
             h.update(fh.read())
     text = open(os.path.join(csrc, "kernels.hpp")).read()
