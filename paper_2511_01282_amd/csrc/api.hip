@@ -167,7 +167,9 @@ respec_status respec_verify_workspace_init(const respec_verify_plan* plan, void*
 
 namespace {
 
-// Streaming attention of a step whose largest tree has n nodes and longest prefix max_kv rows.
+// Streaming attention of a step whose largest tree has n nodes and longest prefix max_kv rows: row
+// waves, key groups, row blocks, rows of a partial block, pieces per (head, row block) and slice of
+// kStreamSlice sequences.
 struct StreamGeom {
   int wr, kg, n_rowblk, part_rows, pieces, slices;
 };
@@ -188,7 +190,8 @@ StreamGeom stream_geom(const respec_verify_plan* p, int n, int max_kv, int batch
   g.part_rows = g.n_rowblk == 1 ? rows : g.wr * 32;
   g.slices = cdiv(batch, kStreamSlice);
   const int heads = p->s.n_kv_heads * g.n_rowblk;
-  // one workgroup per CU, within the partial rows that the workspace holds
+  // one workgroup per CU and slice (one per head and row block at least), within the partial rows
+  // that the workspace holds
   const long long blocks = (long long)(p->part_total / ((size_t)heads * g.part_rows));
   g.pieces = (int)std::max(1ll, std::min((long long)(kCUs / heads), (blocks - batch) / g.slices + 1));
   return g;

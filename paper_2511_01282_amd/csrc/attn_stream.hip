@@ -6,12 +6,14 @@
 // into hi + lo bf16 parts, unnormalised partials (O, m, l) for the split merge.
 //
 // Work split.  A head's 32-row KV tiles over all sequences of the batch are cut
-// into `pieces` intervals of equal cost, one workgroup each (one workgroup per
-// CU: pieces * heads * row blocks is at most the CU count), so that neither a
-// ragged batch nor an odd split count leaves CUs idle.  A piece is a list of
-// segments (sequence, tile range); a sequence's partials are numbered piece +
-// sequence, which is unique and compact (consecutive sequences share at most
-// one piece).
+// into `pieces` intervals of equal cost, one workgroup each, so that neither a
+// ragged batch nor an odd split count leaves CUs idle.  pieces * heads * row
+// blocks is at most the CU count, one workgroup per CU, with two exceptions:
+// more heads * row blocks than CUs have one piece each, and every 256 sequences
+// of a larger batch (a slice) have pieces of their own; those workgroups follow
+// one another.  A piece is a list of segments (sequence, tile range); a
+// sequence's partials are numbered piece + sequence, which is unique and compact
+// (consecutive sequences share at most one piece).
 //
 // Stream.  A ring of S LDS slots (32 rows of K and of V each) is filled by DMA
 // (global_load_lds, 16 bytes per lane).  A segment is a sequence of passes, one

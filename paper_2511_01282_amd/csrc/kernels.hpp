@@ -30,15 +30,16 @@ struct AttnArgs {
   int32_t total_nodes, hidden_size, n_kv_heads, group, kv_cap, max_nodes;
   int32_t nsplit, chunk, n_rowblk, rows_per_wg, wr, wk;
   float scale_log2;        // log2(e) / sqrt(D)
-  // flat > 0 (register path, 2-64 sequences): blockIdx.x is one of `flat` equal pieces of
+  // flat > 0 (tree_attn_kernel, 2-64 sequences): blockIdx.x is one of `flat` equal pieces of
   // the KV tiles of every sequence of its head (partial slots per sequence, nsplit = flat);
-  // 0: blockIdx.x is a split of `chunk` rows of sequence blockIdx.z
+  // 0 (tree_attn_kernel, tree_attn_shared_kernel): blockIdx.x is a split of `chunk` rows of
+  // sequence blockIdx.z (nsplit == 1 in tree_attn_kernel: x is written without partials)
   int32_t flat;
   int32_t batch;
   // streaming kernel (bf16): pieces per (KV head, row block) and slice of sequences; a segment's
   // partial block is slice * (pieces - 1) + piece + sequence, of part_blocks per (head, row block),
   // each part_rows rows; span [B][Hkv][n_rowblk][2]: first and last piece of each sequence.
-  // pieces == 0: the partials of tree_attn_kernel.  One sequence has min(pieces, tiles >> piece_shift)
+  // pieces == 0: the partials of the kernels of attention.hip.  One sequence has min(pieces, tiles >> piece_shift)
   // pieces (at least one), and no span.
   int32_t pieces, part_blocks, part_rows, piece_shift;
   int32_t* span;
