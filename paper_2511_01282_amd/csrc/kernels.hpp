@@ -150,8 +150,8 @@ hipError_t set_tree_attn_stream_lds_limit(int head_dim);
 // Kernels and tiles of the LM head, token rows x vocabulary rows (64 in the plain kernel)
 enum class LmTile {
   kPlain16, kPlain32, kPlain48, kPlain64,
-  kGemm64x256, kGemm128x128,
-  kPair192x128, kPair256x128, kPair128x256, kPair160x256, kPair192x256, kPair224x256, kPair256x256
+  kGemm64x256, kGemm128x128, kGemm256x128,
+  kPair192x128, kPair128x256, kPair160x256, kPair192x256, kPair224x256, kPair256x256
 };
 LmTile lm_tile(int dtype, int m_rows, int vocab);
 int lm_tile_rows(LmTile tile);

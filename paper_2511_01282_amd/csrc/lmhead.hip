@@ -366,9 +366,9 @@ __global__ __launch_bounds__(256, 2) void lmhead_persistent_kernel(LmArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// GEMM variant (bf16), fed by DMA, in two tile shapes: MT = 128 token rows by
-// VR = 128 vocabulary rows (from 65 rows on where lm_tile finds its rounds
-// shortest, mostly 65 to 128), and MT = 64 by VR = 256 (at most 64 rows; each x
+// GEMM variant (bf16), fed by DMA, in three tile shapes: MT = 128 or 256 token rows
+// by VR = 128 vocabulary rows (from 65 rows on where lm_tile finds their rounds
+// shortest, mostly 65 to 128 and 193 to 256), and MT = 64 by VR = 256 (at most 64 rows; each x
 // row then serves four times as many W rows as in the plain kernel), the last
 // of them lower where that spreads them over more CUs (LmArgs::full_tiles,
 // `Tail`; a form without those tests where all are whole: the step of 64 nodes on
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(256, 2) void lmhead_persistent_kernel(LmArgs a) {
 // and x a workgroup needs crosses its CU once:
 //   - K advances in 128-byte steps (64 elements); the W and x rows of a step go
 //     straight from memory into an LDS stage by DMA (global_load_lds, 16 bytes
-//     per lane, no registers), in a ring of S = 4 or 3 stages (32 or 40 KB): after the
+//     per lane, no registers), in a ring of S = 4 or 3 stages (32, 40 or 48 KB): after the
 //     barrier that publishes step c (every wave has finished step c-1 by then)
 //     step c+2 is requested into c-1's stage, so two steps are in flight while
 //     one is multiplied (the W and x rows of a step share a stage: giving W a
@@ -651,8 +651,10 @@ struct TileCost {
 //     (65 rows over 70000 words 144 us per step with 128 by 128, 164 with 128 by 256,
 //     over 152064 254 and 268; over 128256, 1.96 rounds of 128 by 256, 214 and 212).
 //     Measured / second best, us: 32000 rows by 142 tokens 72 / 77 (128 by 256),
-//     by 256 (whole step to the logits) 92.4 / 94.5 (128 by 256; 256 by 128 in the
-//     one-barrier kernel of 128 by 128 94.8), by 200 88.3 / 90.3,
+//     by 256 (whole steps of 8 sequences over 1000-8000 rows) 204.3 (256 by 128) / 205.0 (128 by
+//     256; 204.0 with 256 by 128 in the paired kernel), by 200 199.4 / 205.1 / 200.4, 20000 by 256
+//     188.1 / 191.7 / 191.3, 4 sequences of 61 nodes over 300-2000 126.9 / 133.0 / 129.2; with 8192
+//     columns, 16 of 14 over 300-3000, 286 / 300 / 283;
 //     by 288 83 / 89, by 512 106 / 136, by 624 155 / 170, by 896 200 / 215;
 //     128256 rows by 128 210 / 218, by 384 390 / 410, by 510 455 / 560.
 LmTile lm_tile(int dtype, int M, int vocab) {
@@ -663,7 +665,7 @@ LmTile lm_tile(int dtype, int M, int vocab) {
     return M <= 16 ? LmTile::kPlain16 : M <= 32 ? LmTile::kPlain32 : M <= 48 ? LmTile::kPlain48 : LmTile::kPlain64;
   }
   static constexpr TileCost kCosts[] = {
-      {LmTile::kGemm128x128, 128, 128, 50}, {LmTile::kPair192x128, 192, 128, 62}, {LmTile::kPair256x128, 256, 128, 68},
+      {LmTile::kGemm128x128, 128, 128, 50}, {LmTile::kPair192x128, 192, 128, 62}, {LmTile::kGemm256x128, 256, 128, 68},
       {LmTile::kPair128x256, 128, 256, 71}, {LmTile::kPair160x256, 160, 256, 78}, {LmTile::kPair192x256, 192, 256, 84},
       {LmTile::kPair224x256, 224, 256, 91}, {LmTile::kPair256x256, 256, 256, 97}};
   LmTile best = LmTile::kPair256x256;
@@ -737,10 +739,11 @@ hipError_t launch_lmhead(int dtype, LmTile tile, const LmArgs& a, hipStream_t s,
     if (h == 0 || h == 4) return launch_k(lmhead_gemm_kernel<64, 256, false>, grid, blk, 0, s, nullptr, ev_stop, a);
     return launch_k(lmhead_gemm_kernel<64, 256, true>, grid, blk, 0, s, nullptr, ev_stop, t);
   }
-  if (tile == LmTile::kGemm128x128) {
-    const int n = (a.vocab + 127) / 128;
-    return launch_k(lmhead_gemm_kernel<128, 128, false>, dim3((n + 7) / 8 * 8 * a.n_mtiles), blk, 0, s, nullptr, ev_stop,
-                    a);
+  if (tile <= LmTile::kGemm256x128) {
+    const dim3 grid((a.vocab + 1023) / 1024 * 8 * a.n_mtiles);
+    if (tile == LmTile::kGemm128x128)
+      return launch_k(lmhead_gemm_kernel<128, 128, false>, grid, blk, 0, s, nullptr, ev_stop, a);
+    return launch_k(lmhead_gemm_kernel<256, 128, false>, grid, blk, 0, s, nullptr, ev_stop, a);
   }
   return launch_lmhead_pair(tile, a, s, ev_stop);
 }

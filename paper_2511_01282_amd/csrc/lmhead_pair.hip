@@ -5,13 +5,11 @@
 // What bounds it: matrix-core time, and at a steady load the card's power (256 x 256
 // tiles over 128256 x 4096 columns by 510 rows: 435 us for the first steps after a
 // pause, 455-490 us later; the 256-token by 128-row tiles of one barrier per step
-// that this replaced took 560 and 630-650 us).  At 256 tokens by 128 vocabulary rows
-// a CU's LDS moves 176 KB per 64-column step (128 KB of fragments, 48 KB of DMA),
-// more cycles than the step's products; at 256 x 256 it moves 256 KB for twice the
-// products, as many cycles as the products take.  Below that the W stream bounds
-// it: 193-256 tokens over at most 256 tiles of 128 vocabulary rows take those (W
-// crosses every CU once and the round is full: 256 tokens by 32000 words, steps to
-// the logits, 92.4 us against 94.5 with 128 tokens by 256 rows).
+// took 560 and 630-650 us).  At 256 tokens by 128 vocabulary rows a CU's LDS moves
+// 176 KB per 64-column step (128 KB of fragments, 48 KB of DMA), more cycles than
+// the step's products; at 256 x 256 it moves 256 KB for twice the products, as many
+// cycles as the products take.  (One round of the former is bound by what a CU takes
+// in and stays in the kernel of one barrier per step: lm_tile.)
 //
 //   - Eight waves, two per SIMD, in two groups of four (waves w and w + 4 share a
 //     SIMD).  A phase is a load part (fragments from LDS, DMA requests, the wait for
@@ -294,7 +292,6 @@ hipError_t go(const LmArgs& a, hipStream_t s, hipEvent_t ev_stop) {
 hipError_t launch_lmhead_pair(LmTile tile, const LmArgs& a, hipStream_t s, hipEvent_t ev_stop) {
   switch (tile) {
     case LmTile::kPair192x128: return go<2, 3, 4, 3>(a, s, ev_stop);
-    case LmTile::kPair256x128: return go<2, 4, 4, 3>(a, s, ev_stop);
     case LmTile::kPair128x256: return go<4, 4, 3, 3>(a, s, ev_stop);
     case LmTile::kPair160x256: return go<4, 5, 3, 2>(a, s, ev_stop);
     case LmTile::kPair192x256: return go<4, 6, 3, 2>(a, s, ev_stop);
