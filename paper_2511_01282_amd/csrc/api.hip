@@ -320,6 +320,7 @@ respec_status step_impl(const respec_verify_plan* plan, const respec_verify_args
     const Splits sp = kv_splits(kCUs, a.batch, s.n_kv_heads, t_tiles, 2, held(s.n_kv_heads));
     at.nsplit = sp.n;
     at.chunk = sp.tiles * kKvTile;
+    at.rotate = tiles_rotated(s.head_dim, a.batch, a.kv_capacity);
     merge_rows_per_blk = rows;
     ae = launch_tree_attn_shared(s.head_dim, dim3(at.nsplit, s.n_kv_heads, a.batch), at, st, ev ? ev[0] : nullptr);
   } else if (path == AttnPath::kStream) {

@@ -981,7 +981,7 @@ __global__ __launch_bounds__(512) void tree_attn_shared_kernel(AttnArgs a) {
   const int kv_hi = min(kv_lo + a.chunk, t_rows);
   const int n_tiles = kv_lo < kv_hi ? (kv_hi - kv_lo + kKvTile - 1) / kKvTile : 0;
   const int t_last = max(kv_hi - 1, 0);
-  const int rot = n_tiles > 0 ? tile_rotation(n_tiles) : 0;
+  const int rot = a.rotate && n_tiles > 0 ? tile_rotation(n_tiles) : 0;
   auto tile_row = [&](int i) {  // (row of the i-th tile of the rotated order)
     const int x = i + rot;
     return i < n_tiles ? kv_lo + (x >= n_tiles ? x - n_tiles : x) * kKvTile : t_last;

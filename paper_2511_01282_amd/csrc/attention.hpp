@@ -24,7 +24,7 @@ __device__ __forceinline__ SeqRows seq_rows(const AttnArgs& a, int b) {
 // A workgroup's KV tiles are taken in rotated order, from a start that differs from
 // workgroup to workgroup: heads and pieces lie at regular distances, and
 // workgroups that all walk their tiles from the first one meet on the same
-// memory channels where a head's rows take near a multiple of 2 MB plus or minus
+// memory channels where a head's rows take near a multiple of 512 KB plus or minus
 // 32 KB.  The start is quadratic in the head: one that is linear (or none) moves
 // the meeting to other cache capacities.  33 nodes of 32 heads over 15800 rows, us per
 // attention layer at 50 capacities of 15872 to 16656 rows: by 5 x alone 55.4-69.3, by

@@ -75,6 +75,19 @@ inline AttnPath attn_path(int es, int head_dim, int n_kv_heads, int batch, int r
   return AttnPath::kStream;
 }
 
+// Whether the shared-tile kernel takes a split's tiles in rotated order (tile_rotation in attention.hpp).  In
+// order, the splits of a few sequences meet on the same memory channels where the heads lie near a multiple
+// of 512 KB plus or minus 32 KB apart (65 nodes of 32 heads over 16384 rows, in order / rotated: capacity
+// 16512 68.0 / 61.7 us, 20608 64.4 / 60.6, at six others 59.6-61.8 / 60.2-61.7; in order, of 170 capacities up
+// to 20800 those above 63 us lie 28-48 KB off a multiple); elsewhere they keep out of each other's way, and a short split ends with its masked tiles (over 48000 rows 150 / 155; 2 sequences of 48
+// nodes over 200-1000 rows 19.6 / 21.4).  More sequences, of unlike lengths: rotated (24 of 48 nodes, 32
+// heads of 64 columns, over 500-4000 rows 105 / 101).
+inline bool tiles_rotated(int head_dim, int batch, int kv_capacity) {
+  const long long span = 1 << 19, stride = 2ll * head_dim * kv_capacity, off = (stride + span / 2) % span - span / 2;
+  const long long apart = off < 0 ? -off : off;
+  return batch > 4 || (apart >= 20480 && apart <= 51200);
+}
+
 inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 inline int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 

@@ -43,6 +43,7 @@ struct AttnArgs {
   // pieces (at least one), and no span.
   int32_t pieces, part_blocks, part_rows, piece_shift;
   int32_t* span;
+  int32_t rotate;          // shared tiles: a split's tiles in rotated order (tiles_rotated)
 };
 
 constexpr int kStreamSlice = 256;  // sequences per slice of the streaming kernel

@@ -19,6 +19,7 @@ extern "C" void splits(int wgs, int batch, int heads, long long tiles, int least
   out[0] = s.n;
   out[1] = s.tiles;
 }
+extern "C" int rotated(int d, int batch, int cap) { return tiles_rotated(d, batch, cap); }
 extern "C" void row_geometry(int rows, int* out) {
   const RowGeom g = row_geom(rows);
   const int v[6] = {g.nb, g.wr, g.wk, g.rows_per_wg, g.n_rowblk, g.threads};
@@ -44,6 +45,10 @@ def lib():
 
 def path(es, d, hkv, batch, rows, tiles):
     return NAMES[lib().path(es, d, hkv, batch, rows, tiles)]
+
+
+def rotated(d, batch, cap):
+    return bool(lib().rotated(d, batch, cap))
 
 
 def splits(wgs, batch, heads, tiles, least, held):

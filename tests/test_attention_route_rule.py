@@ -59,6 +59,20 @@ def test_rule_edges(args, want):
     assert attn_paths.path(*args) == want
 
 
+ROTATED = [
+    # (D, sequences, KV capacity): rotated
+    ((128, 1, 16449), False), ((128, 1, 16512), True), ((128, 1, 16256), True), ((128, 1, 20608), True),
+    ((128, 1, 16384), False), ((128, 1, 16463), False), ((128, 1, 16464), True), ((128, 1, 16584), True),
+    ((128, 1, 16585), False), ((128, 1, 18273), True), ((128, 1, 18593), True), ((128, 1, 18432), False), ((128, 4, 1061), False), ((128, 5, 1061), True), ((64, 2, 8320), False),
+    ((64, 2, 8448), True), ((128, 1, 2147483647), False),
+]
+
+
+@pytest.mark.parametrize("args,want", ROTATED)
+def test_rotation_edges(args, want):
+    assert attn_paths.rotated(*args) is want
+
+
 def test_splits_cover_every_tile():
     """Any sizes: the splits cover the tiles, none is empty, and the workspace holds them."""
     rng = random.Random(3)
