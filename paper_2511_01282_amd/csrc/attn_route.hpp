@@ -53,7 +53,10 @@ inline AttnPath attn_path(int es, int head_dim, int n_kv_heads, int batch, int r
     // A last row wave with 16 live rows or fewer is half idle in the stream, whose products are 32
     // rows high (32 heads, shared / stream: 65 nodes over 2100-3000 rows 0.92, 100 over 4000 28.1 / 31.3,
     // over 8000 43.7 / 43.8; 96 over 3000 0.94, over 4000 1.12; 128 over 32000 1.15).
-    if (head_dim == 128 && rows <= 128 && half_idle && cu_tiles > 6ll * kCUs && cu_tiles <= 64ll * kCUs)
+    // 65-80 rows at any length (with tiles_rotated; 65 nodes over 16384 rows 61.0 / 63.4, over 48000 150 / 157,
+    // 40 heads 188 / 199; 33 over 17000 59.7 / 60.7 and 40 over 24000 80.0 / 79.3; 97 over 17000 1.04).
+    const bool any_length = rows > 64 && rows <= 80;
+    if (head_dim == 128 && rows <= 128 && half_idle && cu_tiles > 6ll * kCUs && (any_length || cu_tiles <= 64ll * kCUs))
       return AttnPath::kShared;
     return AttnPath::kStream;
   }

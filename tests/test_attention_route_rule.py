@@ -37,6 +37,8 @@ EDGES = [
     ((2, 128, 32, 1, 48, 160), "split"), ((2, 128, 32, 1, 48, 161), "shared"), ((2, 128, 32, 1, 49, 161), "stream"),
     ((2, 128, 32, 1, 96, 100), "stream"), ((2, 128, 32, 1, 97, 100), "shared"), ((2, 128, 32, 1, 97, 48), "stream"),
     ((2, 128, 32, 1, 112, 512), "shared"), ((2, 128, 32, 1, 112, 513), "stream"), ((2, 128, 32, 1, 113, 100), "stream"),
+    ((2, 128, 32, 1, 65, 513), "shared"), ((2, 128, 40, 1, 80, 4000), "shared"), ((2, 128, 32, 1, 81, 100), "stream"),
+    ((2, 128, 32, 1, 48, 512), "shared"), ((2, 128, 32, 1, 48, 513), "stream"), ((2, 64, 32, 1, 65, 513), "stream"),
     ((2, 64, 32, 1, 97, 100), "stream"), ((2, 128, 32, 1, 129, 100), "stream"),
     ((2, 128, 16, 4, 33, 40), "shared"), ((2, 128, 16, 4, 33, 41), "stream"), ((2, 128, 16, 4, 33, 20), "stream"),
     ((2, 128, 16, 5, 33, 40), "stream"), ((2, 64, 32, 2, 112, 21), "shared"), ((2, 64, 32, 2, 113, 21), "stream"),

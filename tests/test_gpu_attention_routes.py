@@ -61,6 +61,7 @@ CASES = {
     "shared-97-rows": (32, 32, 128, [97], [1500], "shared"),
     "shared-112-rows-grouped": (32, 16, 128, [56], [3100], "shared"),
     "shared-65-rows": (32, 32, 128, [65], [1600], "shared"),
+    "shared-65-rows-rotated": (32, 32, 128, [65], [16400], "shared"),
     "shared-33-rows": (32, 32, 128, [33], [5120], "shared"),
     "shared-a-few": (32, 32, 64, [41, 1, 33], [700, 0, 1100], "shared"),
     "shared-a-few-grouped": (32, 16, 128, [9, 40, 2], [33, 700, 0], "shared"),
