@@ -43,8 +43,9 @@
 // splits of 32-key, 16-row products (the earlier kernel): 12 sequences of 24-61
 // nodes over 500-16000 rows, 8 KV heads of 4: 323 -> 120 us (its two splits per
 // sequence left the longest sequence alone on 16 CUs); 32 sequences of 8-48 nodes
-// over 300-4000 rows, 32 heads: attention + merge 200 -> 194 us (4.2 TB/s); one
-// tree of 64 nodes over 32768 rows, 8 heads of 4: 65 -> 59 us.
+// over 300-4000 rows, 32 heads: attention + merge 200 -> 194 us (4.2 TB/s).  One
+// tree of 64 nodes over 32768 rows, 8 heads of 4, gains little: 67.6 us then,
+// 62.4-65.3 in four traces of this kernel on other cards.
 //
 // Matrix cores: v_mfma_f32_32x32x16_bf16.  A lane then holds 16 scores of ONE
 // query row (the other 16 keys of the tile are in lane ^ 32), so the row
